@@ -73,7 +73,7 @@ COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 def _rt(k):
     """Template count of a dispatched kernel (the generic instance is 0)."""
-    return k if k in (1, 2, 4, 8, 16) else 0
+    return k if k <= 8 else 0
 
 
 def round_kernels(w):
@@ -84,13 +84,13 @@ def round_kernels(w):
     ks = []
     r = w.H if w.H > 1 else w.R
     if w.H > 1:
-        wire = "k_wire<%d>" % w.R if _rt(w.R) else "k_step<0, 3, false>"
+        wire = "k_reduce<%d, 3, false, %d>" % (_rt(w.R), 2 if w.R == 1 else 1)
         ks.append((wire, 2 * w.R * n, 2 * n))
     if w.max_grad_norm > 0 and w.H == 1 and w.clip_scratch:
-        ks.append(("k_step<%d, 1, true>" % _rt(w.R), 2 * w.R * n, 4 * n))
+        ks.append(("k_reduce<%d, 1, true, 1>" % _rt(w.R), 2 * w.R * n, 4 * n))
         ks.append(("k_step<1, 2, false>", 16 * n, 14 * n))
     elif w.max_grad_norm > 0:
-        ks.append(("k_step<%d, 4, true>" % _rt(r), 2 * r * n, 0))
+        ks.append(("k_reduce<%d, 4, true, %d>" % (_rt(r), 4 if r <= 2 else 1), 2 * r * n, 0))
         ks.append(("k_step<%d, 0, false>" % _rt(r), (2 * r + 12) * n, 14 * n))
     else:
         ks.append(("k_step<%d, 0, true>" % _rt(r), (2 * r + 12) * n, 14 * n))
@@ -273,9 +273,9 @@ def step_label(w):
                                          "per-segment sums")
     parts = []
     if w.H > 1:
-        parts.append("k_wire<R=%d>" % w.R)
+        parts.append("k_reduce<R=%d, wire>" % w.R)
     if w.max_grad_norm > 0:
-        parts.append("k_step<%s=%d, sum of squares> + finalize" % (
+        parts.append("k_reduce<%s=%d, sum of squares> + finalize" % (
             "R" if w.H == 1 else "H", w.R if w.H == 1 else w.H))
     parts.append(fused)
     return "one local step: " + " + ".join(parts)

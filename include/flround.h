@@ -141,10 +141,10 @@ typedef struct {
  *   layout's workspace (see fl_layout_create).  A small finalize kernel
  *   folds the pass's per-tile partials into the per-segment totals.  In
  *   fl_round, fl_round_outer, fl_round_noalloc and fl_round_hsdp, when every
- *   segment spans at most 1024 tiles and there are at most 8 segments, one
- *   extra workgroup of the round's next kernel (the next step, or the
- *   FedAvg or broadcast pass) does that fold instead, with the same fixed
- *   trees and the same bits, while the rest of the kernel streams.
+ *   segment spans at most 1024 tiles and there are at most 8 segments, extra
+ *   workgroups of the round's next kernel (the next step, or the FedAvg or
+ *   broadcast pass) do that fold instead, with the same fixed trees and the
+ *   same bits, while the rest of the kernel streams.
  * 1 <= R <= FL_MAX_PEERS; grad_scale finite.
  * ---------------------------------------------------------------------- */
 int fl_shard_reduce(const fl_layout* layout, int R, const uint16_t* const* peer_grads,
@@ -434,10 +434,11 @@ int fl_round_hsdp(const fl_layout* layout, const fl_round_cfg* cfg, const fl_hsd
 /* ------------------------------------------------------------------------
  * Launch-shape control, for tuning sweeps and for tests that check that
  * results do not depend on the launch shape.  blocks_per_cu > 0 caps the
- * grid of every streaming kernel at blocks_per_cu * (number of CUs); 0
- * restores the defaults (one workgroup per CU for the fused step and the
- * FedAvg-side passes, more for the passes that only read the peer gradients,
- * by R).  Process-wide; returns the previous value.
+ * grid of every streaming kernel at blocks_per_cu * (number of CUs)
+ * workgroups of 256 threads (four times as many of one wave); 0 restores the
+ * defaults (a wave for every 512 elements, started in order, with a limit per
+ * pass on how many a CU holds at once).  Process-wide; returns the previous
+ * value.
  * ---------------------------------------------------------------------- */
 int fl_set_blocks_per_cu(int blocks_per_cu);
 

@@ -7,10 +7,11 @@
 
 namespace flr {
 
-constexpr int kBlock = 256;            // threads per workgroup (4 wave64)
+constexpr int kBlock = 256;            // threads of a tile, and of a finalize workgroup
 constexpr int kVec = 8;                // elements per thread per tile (16 B of bf16)
-constexpr int kTile = kBlock * kVec;   // elements per tile: 2048
-constexpr int kWaves = kBlock / 64;    // wave64s per workgroup: one partial slot each
+constexpr int kTile = kBlock * kVec;   // elements per tile of the segment tables: 2048
+constexpr int kUnit = 64 * kVec;       // elements a wave64 takes at a time: 512
+constexpr int kWaves = kTile / kUnit;  // units per tile: one partial slot each
 constexpr int kChunkPieces = 1024;    // pieces folded by one workgroup in the finalize
 constexpr int kCarryMaxChunks = 8;    // finalize carried by the next kernel up to this many chunks
 constexpr int kMaxPeers = 64;
@@ -48,9 +49,9 @@ struct LayoutDev {
 };
 
 // The finalize of the previous pass of a call, carried by the call's next
-// kernel: that kernel runs one extra workgroup (its last) which folds the
-// (piece, wave) partials the previous pass wrote, with the trees of
-// k_seg_chunks, while the other workgroups stream.  Only for layouts whose
+// kernel: that kernel runs kCarryMaxChunks extra workgroups (its first) which
+// fold the (piece, wave) partials the previous pass wrote, one chunk each,
+// with the trees of k_seg_chunks, while the other workgroups stream.  Only for layouts whose
 // every segment is one finalize chunk (chunk c is segment c) and that have at
 // most kCarryMaxChunks of them.  partials == null: nothing carried.
 struct Carry {
@@ -110,20 +111,29 @@ struct BcastArgs {
   Carry carry;
 };
 
-hipError_t launch_local_step(const StepArgs& a, int grid, hipStream_t st);
-hipError_t launch_reduce(const StepArgs& a, int grid, hipStream_t st);
-hipError_t launch_adamw(const StepArgs& a, int grid, hipStream_t st);
-hipError_t launch_reduce_wire(const StepArgs& a, int grid, hipStream_t st);
-hipError_t launch_bcast_recv(const BcastArgs& a, int grid, hipStream_t st);
-hipError_t launch_fedavg(const FedArgs& a, int grid, hipStream_t st);
-// The launch helpers take `grid` workgroups for the stream and add one for a
-// carried finalize (a.carry.partials set).
+// Launch shape of a streaming pass: workgroups of one wave, units each takes
+// at a time, and the LDS each asks for (it uses none), which bounds how many a
+// CU holds at once.
+struct Shape {
+  unsigned grid;
+  int units;
+  unsigned lds;
+};
+
+hipError_t launch_local_step(const StepArgs& a, Shape sh, hipStream_t st);
+hipError_t launch_reduce(const StepArgs& a, Shape sh, hipStream_t st);
+hipError_t launch_adamw(const StepArgs& a, Shape sh, hipStream_t st);
+hipError_t launch_reduce_wire(const StepArgs& a, Shape sh, hipStream_t st);
+hipError_t launch_bcast_recv(const BcastArgs& a, Shape sh, hipStream_t st);
+hipError_t launch_fedavg(const FedArgs& a, Shape sh, hipStream_t st);
+// The launch helpers add the carriers of a carried finalize (a.carry.partials
+// set) to the grid.
 // Per-segment totals from the (piece, wave) partials: chunk_sums
 // (L.n_chunks doubles) and seg_dbl (L.n_seg doubles) are temporaries; out
 // (n_seg floats) and total (one double, the whole shard) may be null.
 hipError_t launch_seg_finalize(const LayoutDev& L, const double* partials, double* chunk_sums,
                                double* seg_dbl, float* out, double* total, hipStream_t st);
-hipError_t launch_sumsq_only(const StepArgs& a, int grid, hipStream_t st);
+hipError_t launch_sumsq_only(const StepArgs& a, Shape sh, hipStream_t st);
 
 // The static scratch of fl_round_noalloc (kNoallocScratchBytes per GPU).
 // The first call for a device, with that device current, looks up the

@@ -46,23 +46,6 @@ namespace {
 
 std::atomic<int> g_blocks_per_cu{0};  // 0: the per-pass defaults below
 
-// Default workgroups per CU.  One 256-thread workgroup per CU keeps enough
-// 16-byte loads in flight for the passes that stream many arrays (the fused
-// step, FedAvg, the optimiser-only and broadcast passes).  A pass that only
-// reads the R peer gradients (the sum-of-squares pass, and the reductions when
-// R is small) has fewer loads in flight per thread and needs more workgroups
-// to cover HBM latency.  Chosen by occupancy sweeps on a 1.0e9-element shard.
-constexpr int kDefaultBlocksPerCu = 1;
-int sumsq_blocks_per_cu(int R) {
-  return R >= 8 ? 2 : R >= 4 ? 3 : R == 3 ? 4 : R == 2 ? 6 : 8;
-}
-int reduce_blocks_per_cu(int R) { return R >= 8 ? 1 : 2; }
-int wire_blocks_per_cu(int R) {
-  const bool two_vector_kernel = R == 1 || R == 2 || R == 4 || R == 8 || R == 16;
-  if (two_vector_kernel) return R <= 2 ? 2 : 1;
-  return R >= 8 ? 1 : 2;
-}
-
 constexpr uint64_t kFnvOffset = 0xCBF29CE484222325ULL;
 constexpr uint64_t kFnvPrime = 0x100000001B3ULL;
 
@@ -172,25 +155,96 @@ int check_device(const fl_layout* lay) {
   return dev == lay->device ? FL_OK : FL_ERR_DEVICE;
 }
 
-// Workgroups of a pass over `units` tiles or vector groups: a grid-stride
-// loop over a grid of bpc workgroups per CU; a shard whose units all fit on
-// the chip at once (at most kResidentPerCu per CU) gets one workgroup per unit
-// instead, so that a small shard is not spread over fewer workgroups than it
-// has tiles.  An explicit fl_set_blocks_per_cu applies to every pass.
-constexpr int kResidentPerCu = 4;
-int grid_for(const fl_layout* lay, int64_t units, int default_bpc = kDefaultBlocksPerCu) {
-  const int set = g_blocks_per_cu.load(std::memory_order_relaxed);
-  if (set <= 0 && units <= (int64_t)kResidentPerCu * lay->num_cus) return (int)(units < 1 ? 1 : units);
-  const int bpc = set > 0 ? set : default_bpc;
-  int64_t cap = (int64_t)bpc * (int64_t)lay->num_cus;
-  if (cap < 1) cap = 1;
-  int64_t g = units < cap ? units : cap;
-  return (int)(g < 1 ? 1 : g);
-}
+// Launch shapes of the streaming passes.
+//
+// What bounds them is HBM, and its rate depends on how close together the
+// addresses are that the chip has in flight.  So a workgroup is one wave that
+// takes one unit (512 elements) and ends: the hardware starts workgroups in
+// index order, which keeps the units in flight a narrow window of each array.
+// (Resident workgroups striding over the shard drift apart: with one such
+// workgroup of four waves per CU the 8B shard's step, R = 8, took 7.60 ms,
+// with two 8.6 ms, with this 6.65 ms.)  And a CU holds only as many waves as
+// cover the latency: more widen the window, fewer leave gaps.  The limit is
+// set by LDS that a workgroup asks for and does not use.
+//
+// The limits are the best of sweeps of 3 to 32 waves per CU on 5e8 elements;
+// the figures are TB/s at the limit taken, and at 32.  The fewer bytes a wave
+// loads, the more waves.
+struct Pass {
+  int waves;      // waves a CU holds at once
+  int mid;        // the same for shards of kSmall to kMid units per CU
+  int small;      // and for shards of kFew to kSmall
+  int units = 1;  // units a workgroup takes at a time
+};
 
-int fedavg_grid(const fl_layout* lay) {
-  const int64_t nvec = (lay->L.n + flr::kVec - 1) / flr::kVec;
-  return grid_for(lay, (nvec + flr::kBlock - 1) / flr::kBlock);
+// step: R=1 5.87/5.49, R=2 5.90/5.45, R=4 5.95/5.41, R=6 5.97/5.47, R=8
+// 6.02/5.59, R=12 6.02/5.63, R=16 5.97/5.56, R=64 5.60/5.42.
+Pass step_pass(int R) {
+  const int w = R <= 2 ? 8 : R <= 4 ? 7 : R <= 12 ? 5 : 4;
+  return {w, w + 2, 2 * w};
+}
+// AdamW alone: 5.83/5.35.
+constexpr Pass kAdamPass = {6, 8, 9};
+// Sums of squares only: R=1 3.99 with four units per workgroup and 3.36 with
+// one, R=2 6.05 and 5.70, R=4 6.47/6.35, R=8 6.70/6.47, R=16 6.68/6.66, R=32
+// 6.75/6.67.
+Pass sumsq_pass(int R) {
+  if (R <= 2) return {24, 24, 24, 4};
+  const int w = R <= 3 ? 24 : R <= 5 ? 20 : R <= 7 ? 14 : R <= 12 ? 10 : 7;
+  return {w, w, 2 * w};
+}
+// To fp32: R=1 5.08/5.19, R=2 5.53/5.58, R=4 6.11/5.91, R=8 6.45/6.10, R=16
+// 6.33/5.89, R=32 5.95/5.75.
+Pass reduce_pass(int R) {
+  const int w = R <= 3 ? 24 : R <= 6 ? 12 : R <= 12 ? 8 : 6;
+  return {w, w, 2 * w};
+}
+// To the wire format: R=1 6.75 with two units per workgroup and 6.44 with
+// one, R=2 6.78/6.78, R=4 6.94/6.38, R=8 6.68/6.21, R=16 6.52/6.21, R=32
+// 6.38/6.03.
+Pass wire_pass(int R) {
+  if (R == 1) return {20, 20, 20, 2};
+  const int w = R == 2 ? 32 : R == 3 ? 16 : R <= 5 ? 12 : R == 6 ? 9 : R <= 8 ? 7 : 6;
+  return {w, w, 2 * w};
+}
+// FedAvg: G=1 5.64/3.58, G=2 6.02/4.23, G=4 6.40/5.83, G=5 6.45/6.06, G=8
+// 6.62/6.05, G=16 6.26/5.87.  With the outer step: G=2 5.66/5.24, G=4
+// 5.65/5.32, G=8 5.97/5.39.
+Pass fedavg_pass(int G, bool outer) {
+  const int w = outer ? 5 : G == 1 ? 14 : G == 2 ? 10 : G <= 4 ? 9 : G <= 5 ? 8 : G <= 7 ? 7
+              : G <= 12 ? 6 : 5;
+  return {w, w, 2 * w};
+}
+// Broadcast receive: 5.49/3.98.
+constexpr Pass kBcastPass = {12, 12, 12};
+
+// Shorter passes gain from more waves, as the ramps at both ends count for
+// more and the window for less: the step at R = 8 on 27e6 elements runs at
+// 6.17 TB/s with 7 waves and 6.04 with 5, at R = 2 on 8e6 elements at 5.99
+// with 16 and 5.45 with 8, on 2e6 (15 units per CU) at 5.58 without a limit
+// and 5.62 with 16, 4.95 with 8.
+constexpr int64_t kMid = 384, kSmall = 100, kFew = 20;
+constexpr int64_t kMaxGrid = (int64_t)1 << 25;  // x 64 threads: within 2^32
+constexpr int kCuLds = 160 << 10;               // bytes of LDS of a CU
+constexpr int kLdsStep = 1280;                  // allocated in steps of this
+constexpr int kCuWaves = 32;                    // waves a CU can hold
+
+// An explicit fl_set_blocks_per_cu caps the grid instead (in workgroups of
+// kBlock threads), and the kernels' grid-stride loops cover the rest.
+flr::Shape shape_for(const fl_layout* lay, Pass pass) {
+  const int64_t per_cu = lay->L.n_tiles * flr::kWaves / lay->num_cus;
+  // a short pass needs every wave it has
+  flr::Shape sh{1, per_cu < kSmall ? 1 : pass.units, 0};
+  int64_t blocks = lay->L.n_tiles * (flr::kWaves / sh.units);
+  const int set = g_blocks_per_cu.load(std::memory_order_relaxed);
+  if (set > 0) {
+    blocks = std::min<int64_t>(blocks, (int64_t)set * lay->num_cus * flr::kWaves);
+  } else if (per_cu > kFew) {
+    const int limit = per_cu >= kMid ? pass.waves : per_cu >= kSmall ? pass.mid : pass.small;
+    if (limit < kCuWaves) sh.lds = (unsigned)(kCuLds / limit / kLdsStep * kLdsStep);
+  }
+  sh.grid = (unsigned)std::max<int64_t>(1, std::min(blocks, kMaxGrid));
+  return sh;
 }
 
 int status_of(hipError_t e) {
@@ -375,14 +429,12 @@ int enqueue_local_step(const fl_layout* lay, const fl_adamw_hparams& h, int64_t 
   for (int r = 0; r < R; ++r) a.grads[r] = peers[r];
   a.R = R;
   a.grad_scale = grad_scale;
-  const int grid = grid_for(lay, lay->L.n_tiles);
   int rc = FL_OK;
   take_carry(a, pending);
   if (clip_max > 0.f && g_scratch) {
     a.partials = free_slot(ws, a.carry);
     a.g_out = g_scratch;
-    rc = status_of(flr::launch_reduce(a, grid_for(lay, lay->L.n_tiles, reduce_blocks_per_cu(R)),
-                                      st));
+    rc = status_of(flr::launch_reduce(a, shape_for(lay, reduce_pass(R)), st));
     if (rc == FL_OK)
       rc = status_of(flr::launch_seg_finalize(lay->L, a.partials, ws.chunks, ws.seg, seg_sumsq,
                                               ws.total, st));
@@ -395,13 +447,12 @@ int enqueue_local_step(const fl_layout* lay, const fl_adamw_hparams& h, int64_t 
     b.working = working;
     b.clip_total = ws.total;
     b.clip_max = clip_max;
-    if (rc == FL_OK) rc = status_of(flr::launch_adamw(b, grid, st));
+    if (rc == FL_OK) rc = status_of(flr::launch_adamw(b, shape_for(lay, kAdamPass), st));
     return rc;
   }
   if (clip_max > 0.f) {
     a.partials = free_slot(ws, a.carry);
-    rc = status_of(flr::launch_sumsq_only(a, grid_for(lay, lay->L.n_tiles,
-                                                      sumsq_blocks_per_cu(R)), st));
+    rc = status_of(flr::launch_sumsq_only(a, shape_for(lay, sumsq_pass(R)), st));
     if (rc == FL_OK)
       rc = status_of(flr::launch_seg_finalize(lay->L, a.partials, ws.chunks, ws.seg, seg_sumsq,
                                               ws.total, st));
@@ -417,7 +468,7 @@ int enqueue_local_step(const fl_layout* lay, const fl_adamw_hparams& h, int64_t 
   a.v = v;
   a.working = working;
   if (seg_sumsq) a.partials = free_slot(ws, a.carry);
-  if (rc == FL_OK) rc = status_of(flr::launch_local_step(a, grid, st));
+  if (rc == FL_OK) rc = status_of(flr::launch_local_step(a, shape_for(lay, step_pass(R)), st));
   if (rc == FL_OK && seg_sumsq) rc = finish_sums(lay, ws, a.partials, seg_sumsq, pending, st);
   return rc;
 }
@@ -449,7 +500,7 @@ int enqueue_fedavg(const fl_layout* lay, int G, const uint16_t* const* reps, con
   }
   f.master = master;
   f.working = working;
-  return status_of(flr::launch_fedavg(f, fedavg_grid(lay), st));
+  return status_of(flr::launch_fedavg(f, shape_for(lay, fedavg_pass(G, outer != nullptr)), st));
 }
 
 int enqueue_bcast(const fl_layout* lay, const float* recv, float* master, uint16_t* working,
@@ -461,7 +512,7 @@ int enqueue_bcast(const fl_layout* lay, const float* recv, float* master, uint16
   b.recv = recv;
   b.master = master;
   b.working = working;
-  return status_of(flr::launch_bcast_recv(b, fedavg_grid(lay), st));
+  return status_of(flr::launch_bcast_recv(b, shape_for(lay, kBcastPass), st));
 }
 
 }  // namespace
@@ -584,9 +635,10 @@ int fl_layout_create(int64_t n, int64_t n_seg, const int64_t* seg_offsets,
   const size_t b_pp = sizeof(int64_t) * (size_t)(n_seg + 1);
   const size_t b_sc = sizeof(int64_t) * (size_t)(n_seg + 1);
   const size_t b_cp = sizeof(int64_t) * (size_t)(n_chunks + 1);
+  const size_t b_pad = ((size_t)0 - (b_off + b_pp + b_sc + b_cp)) & 15;  // tiles on 16 bytes
   const size_t b_tiles = sizeof(flr::TileInfo) * (size_t)n_tiles;
   const size_t b_dec = (size_t)n_seg;
-  const size_t b_tables = (b_off + b_pp + b_sc + b_cp + b_tiles + b_dec + 255) & ~(size_t)255;
+  const size_t b_tables = (b_off + b_pp + b_sc + b_cp + b_pad + b_tiles + b_dec + 255) & ~(size_t)255;
   const size_t b_ws = n > 0 ? ws_bytes(lay->L) : 0;
   const size_t total = b_tables + b_ws + 64;
   void* mem = nullptr;
@@ -610,7 +662,7 @@ int fl_layout_create(int64_t n, int64_t n_seg, const int64_t* seg_offsets,
   char* p_pp = p_off + b_off;
   char* p_sc = p_pp + b_pp;
   char* p_cp = p_sc + b_sc;
-  char* p_tiles = p_cp + b_cp;
+  char* p_tiles = p_cp + b_cp + b_pad;
   char* p_dec = p_tiles + b_tiles;
   e = hipMemcpy(p_off, seg_offsets, b_off, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(p_pp, seg_piece0.data(), b_pp, hipMemcpyHostToDevice);
@@ -684,8 +736,7 @@ int fl_shard_reduce(const fl_layout* layout, int R, const uint16_t* const* peer_
   a.grad_scale = grad_scale;
   a.g_out = grad_out;
   a.partials = ws.p;
-  rc = status_of(flr::launch_reduce(a, grid_for(layout, layout->L.n_tiles,
-                                                reduce_blocks_per_cu(R)), st));
+  rc = status_of(flr::launch_reduce(a, shape_for(layout, reduce_pass(R)), st));
   if (rc == FL_OK && seg_sumsq)
     rc = status_of(flr::launch_seg_finalize(layout->L, ws.p, ws.chunks, ws.seg, seg_sumsq,
                                             nullptr, st));
@@ -714,7 +765,7 @@ int fl_adamw_step(const fl_layout* layout, const fl_adamw_hparams* h, int64_t st
   a.m = m;
   a.v = v;
   a.working = working;
-  return status_of(flr::launch_adamw(a, grid_for(layout, layout->L.n_tiles),
+  return status_of(flr::launch_adamw(a, shape_for(layout, kAdamPass),
                                      static_cast<hipStream_t>(stream)));
 }
 
@@ -782,8 +833,7 @@ int fl_grad_sumsq(const fl_layout* layout, int R, const uint16_t* const* peer_gr
   a.R = R;
   a.grad_scale = grad_scale;
   a.partials = ws.p;
-  rc = status_of(flr::launch_sumsq_only(a, grid_for(layout, layout->L.n_tiles,
-                                                    sumsq_blocks_per_cu(R)), st));
+  rc = status_of(flr::launch_sumsq_only(a, shape_for(layout, sumsq_pass(R)), st));
   if (rc == FL_OK)
     rc = status_of(flr::launch_seg_finalize(layout->L, ws.p, ws.chunks, ws.seg, seg_sumsq,
                                             total_sumsq, st));
@@ -820,7 +870,7 @@ int fl_local_step_clipped(const fl_layout* layout, const fl_adamw_hparams* h, in
   a.working = working;
   a.clip_total = total_sumsq;
   a.clip_max = max_norm;
-  return status_of(flr::launch_local_step(a, grid_for(layout, layout->L.n_tiles),
+  return status_of(flr::launch_local_step(a, shape_for(layout, step_pass(R)),
                                           static_cast<hipStream_t>(stream)));
 }
 
@@ -839,8 +889,7 @@ int fl_shard_reduce_wire(const fl_layout* layout, int R, const uint16_t* const* 
   a.R = R;
   a.grad_scale = grad_scale;
   a.wire_out = wire_out;
-  return status_of(flr::launch_reduce_wire(a, grid_for(layout, layout->L.n_tiles,
-                                                        wire_blocks_per_cu(R)),
+  return status_of(flr::launch_reduce_wire(a, shape_for(layout, wire_pass(R)),
                                            static_cast<hipStream_t>(stream)));
 }
 
@@ -950,8 +999,7 @@ int fl_round_hsdp(const fl_layout* layout, const fl_round_cfg* cfg, const fl_hsd
     t1.R = c.R;
     t1.grad_scale = c.grad_scale;
     t1.wire_out = wire;
-    rc = status_of(flr::launch_reduce_wire(
-        t1, grid_for(layout, layout->L.n_tiles, wire_blocks_per_cu(c.R)), st));
+    rc = status_of(flr::launch_reduce_wire(t1, shape_for(layout, wire_pass(c.R)), st));
     // tier 2: the replication group's average of the H wire shards, fused
     // with the optimiser step
     const uint16_t* wires[FL_MAX_PEERS];

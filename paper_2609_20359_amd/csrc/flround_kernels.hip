@@ -3,22 +3,23 @@
 // Every kernel here is a bandwidth-bound stream over the flat shard: an
 // element is read once, updated with a few dozen fp32 operations and written
 // once, so the kernels are built for HBM, not for the matrix cores:
-//   * a workgroup of 256 threads (4 wave64) owns one 2048-element tile per
-//     iteration of a grid-stride loop; each thread owns 8 consecutive
-//     elements, i.e. one 16-byte load per bf16 stream and two per fp32 stream
-//     (global_load_dwordx4), so every wave touches whole 128-byte lines;
-//   * all loads of a tile are issued before its arithmetic (memory-level
-//     parallelism), with compile-time peer / group counts where common;
+//   * a workgroup is one wave64 and takes one unit of 512 elements; each lane
+//     owns 8 consecutive elements, i.e. one 16-byte load per bf16 stream and
+//     two per fp32 stream (global_load_dwordx4), so a wave touches whole
+//     128-byte lines.  The grid has a workgroup for every unit, and how many
+//     a CU holds at once is limited per pass (the launch shapes say why);
+//   * all loads of a unit are out before its arithmetic, the layout table's by
+//     way of the scalar cache: a wave waits for memory once;
 //   * sums over peers and replicas run in ascending index order in fp32, one
 //     correctly rounded operation at a time (the file is built with
 //     -ffp-contract=off), so results are bitwise those of the definition and
 //     do not depend on the grid;
 //   * per-segment sums of squares use wave64 butterfly reductions only: each
 //     lane squares its elements exactly in double, and each wave writes one
-//     double partial per (tile, segment) piece it covers, with no workgroup
-//     barrier in the streaming loop; a small finalize folds the partials per
-//     segment (and, for clipping, over the shard) in fixed trees; only tiles
-//     that straddle a segment boundary (rare) resolve segments per element.
+//     double partial per (tile, segment) piece it covers; a small finalize
+//     folds the partials per segment (and, for clipping, over the shard) in
+//     fixed trees; only units that straddle a segment boundary (rare) resolve
+//     segments per element.
 #include "flr_internal.h"
 
 #include <mutex>
@@ -33,6 +34,7 @@ namespace flr {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -75,6 +77,34 @@ __device__ __forceinline__ void st(T* p, T v) {
   *p = v;
 #endif
 }
+
+// Values that no kernel writes while one reads them (layout tables, the clip
+// total of an earlier kernel) and that a whole wave reads at one address: by
+// way of the constant address space the compiler uses scalar loads, which do
+// not queue behind or stall the streams' vector loads.
+template <typename T>
+__device__ __forceinline__ T ld_uniform(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
+// Asks for a step's kernel arguments at the top of the kernel, all together:
+// left to itself the compiler loads them where they are first used, block by
+// block, and a wave waits for each group in turn before its first data load.
+template <int NP>
+__device__ __forceinline__ void args_in(const StepArgs& a) {
+  asm volatile("" ::"s"(a.carry.partials), "s"(a.L.n), "s"(a.L.n_tiles), "s"(a.L.tiles),
+               "s"(a.master), "s"(a.m), "s"(a.v), "s"(a.working), "s"(a.g_in), "s"(a.partials),
+               "s"(a.clip_total), "s"(a.grad_scale), "s"(a.s.b1), "s"(a.s.omb1), "s"(a.s.b2),
+               "s"(a.s.omb2), "s"(a.s.step_size), "s"(a.s.bc2_sqrt), "s"(a.s.eps),
+               "s"(a.s.decay), "s"(a.grads[0]), "s"(a.grads[1 % NP]), "s"(a.grads[2 % NP]),
+               "s"(a.grads[3 % NP]), "s"(a.grads[4 % NP]), "s"(a.grads[5 % NP]),
+               "s"(a.grads[6 % NP]), "s"(a.grads[7 % NP]));
+}
+
+// Keeps the compiler from moving a stream's loads below the arithmetic before
+// it, which it does to save registers; all of a wave's loads have to be out
+// before it waits for the first.
+__device__ __forceinline__ void loads_out() { __builtin_amdgcn_sched_barrier(0); }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -131,28 +161,56 @@ __device__ __forceinline__ void store_f32x8(float* p, const float x[8]) {
   st(reinterpret_cast<f32x4*>(p + 4), f32x4{x[4], x[5], x[6], x[7]});
 }
 
+// Sum over n bf16 streams of element e of a full vector, streams in ascending
+// order: add(acc, k, w) adds stream k's 8 elements w.  N > 0: n == N, all its
+// loads issued before the first addition; N == 0: n > kChunk, kChunk streams
+// at a time, the next chunk's loads issued before this one's additions.
+constexpr int kChunk = 8;
+
+template <int N, typename Ptr, typename Add>
+__device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
+  if constexpr (N > 0) {
+    u32x4 w[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k)));
+    loads_out();
+#pragma unroll
+    for (int k = 0; k < N; ++k) add(k, w[k]);
+  } else {
+    u32x4 w[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) w[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k)));
+    int k0 = kChunk;
+    for (; k0 + kChunk <= n; k0 += kChunk) {
+      u32x4 x[kChunk];
+#pragma unroll
+      for (int k = 0; k < kChunk; ++k) x[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k0 + k)));
+      loads_out();
+#pragma unroll
+      for (int k = 0; k < kChunk; ++k) {
+        add(k0 - kChunk + k, w[k]);
+        w[k] = x[k];
+      }
+    }
+    u32x4 x[kChunk];
+#pragma unroll
+    for (int k = 0; k < kChunk - 1; ++k)
+      if (k0 + k < n) x[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k0 + k)));
+    loads_out();
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) add(k0 - kChunk + k, w[k]);
+#pragma unroll
+    for (int k = 0; k < kChunk - 1; ++k)
+      if (k0 + k < n) add(k0 + k, x[k]);
+  }
+}
+
 // Reduced gradient of 8 elements (full vector): peers in ascending order.
 template <int RT>
 __device__ __forceinline__ void reduce_vec(const StepArgs& a, int64_t base, float g[8]) {
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if constexpr (RT > 0) {
-    u32x4 w[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) w[r] = ld_once(reinterpret_cast<const u32x4*>(a.grads[r] + base));
-#pragma unroll
-    for (int r = 0; r < RT; ++r) add_bf16x8(acc, w[r]);
-  } else {
-    constexpr int kChunk = 4;
-    for (int r0 = 0; r0 < a.R; r0 += kChunk) {
-      u32x4 w[kChunk];
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k)
-        if (r0 + k < a.R) w[k] = ld_once(reinterpret_cast<const u32x4*>(a.grads[r0 + k] + base));
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k)
-        if (r0 + k < a.R) add_bf16x8(acc, w[k]);
-    }
-  }
+  sum_streams<RT>([&](int r) { return a.grads[r] + base; }, a.R,
+                  [&](int, u32x4 w) { add_bf16x8(acc, w); });
 #pragma unroll
   for (int e = 0; e < 8; ++e) g[e] = acc[e] * a.grad_scale;
 }
@@ -181,8 +239,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Clip coefficient from the whole-shard sum of squares: min(1, max / (norm +
 // 1e-6)) in double, rounded once to float; a NaN norm gives NaN, as torch's
 // clamp does.
-__device__ __forceinline__ float clip_coef(const double* total, float max_norm) {
-  const double c = (double)max_norm / (__builtin_sqrt(*total) + 1e-6);
+__device__ __forceinline__ float clip_coef(double total, float max_norm) {
+  const double c = (double)max_norm / (__builtin_sqrt(total) + 1e-6);
   return (float)(c >= 1.0 ? 1.0 : c);
 }
 
@@ -237,75 +295,181 @@ __device__ __forceinline__ double total_fold(int64_t n_seg, Get get, double* red
   return sum;
 }
 
-// A carried finalize (see Carry): the last workgroup of a kernel launched
-// with one extra workgroup folds the previous pass's partials, chunk by
-// chunk, with the tree of k_seg_chunks, and writes each segment's float sum;
-// returns true in that workgroup (which then has nothing else to do).  Every
-// workgroup calls it first; the others stream over work units blockIdx.x ..
-// in steps of gridDim.x - carried, exactly as without the extra workgroup.
-// That keeps the workgroup -> tile mapping, and so the XCD that touches each
-// tile, the same in consecutive kernels: at small shard sizes the next pass
-// then finds the tile in that XCD's L2.  The partials come from an earlier
-// kernel of the same stream, so plain loads see them.
+// The chunk total of chunk_fold by one wave64: each lane stands for threads
+// lane, lane + 64, lane + 128 and lane + 192 of that tree, so the bits are the
+// same.  Their four loads go out together: with one after another the fold of
+// a short pass (512 pieces) outlasts the pass that carries it.
+__device__ __forceinline__ double chunk_fold_wave(const int64_t* chunk_p0, const double* partials,
+                                                  int64_t c) {
+  const int64_t p0 = chunk_p0[c];
+  const int64_t p1 = chunk_p0[c + 1];
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) {
+    f64x2 w0[4], w1[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t pk = p + 64 * k < p1 ? p + 64 * k : p;
+      w0[k] = *reinterpret_cast<const f64x2*>(partials + pk * kWaves);
+      w1[k] = *reinterpret_cast<const f64x2*>(partials + pk * kWaves + 2);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (p + 64 * k < p1) {
+        acc[k] = acc[k] + w0[k].x;
+        acc[k] = acc[k] + w0[k].y;
+        acc[k] = acc[k] + w1[k].x;
+        acc[k] = acc[k] + w1[k].y;
+      }
+    }
+  }
+  double w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = wave_sum(acc[k]);
+  return ((w[0] + w[1]) + w[2]) + w[3];
+}
+
+// A carried finalize (see Carry): the first kCarryMaxChunks workgroups of a
+// kernel launched with that many more fold the previous pass's partials, one
+// chunk each, with the tree of k_seg_chunks, and write each segment's float
+// sum; returns true in those (which then have nothing else to do).  Every
+// workgroup calls it first; the others take their units from index
+// blockIdx.x - carried.  Workgroups go to the eight XCDs round robin, so with
+// eight in front every unit stays on the XCD that has it without a carry: at
+// small shard sizes the next pass finds the unit in that XCD's L2.  In front,
+// the fold runs while the others stream, also when the grid does not fit on
+// the chip at once.  The partials come from an earlier kernel of the same
+// stream, so plain loads see them.
+static_assert(kCarryMaxChunks % 8 == 0, "carriers must not move units to other XCDs");
+
 __device__ __forceinline__ bool run_carry(const Carry& c) {
-  if (c.partials == nullptr || blockIdx.x != gridDim.x - 1) return false;
-  __shared__ double red[4];
-  for (int64_t k = 0; k < c.n_chunks; ++k) {
-    const double sum = chunk_fold(c.chunk_p0, c.partials, k, red);
-    if (threadIdx.x == 0) c.out[k] = (float)sum;
+  if (c.partials == nullptr || blockIdx.x >= kCarryMaxChunks) return false;
+  if (blockIdx.x < c.n_chunks) {
+    const double sum = chunk_fold_wave(c.chunk_p0, c.partials, blockIdx.x);
+    if (threadIdx.x == 0) c.out[blockIdx.x] = (float)sum;
   }
   return true;
 }
 
-__device__ __forceinline__ int carried(const Carry& c) { return c.partials != nullptr ? 1 : 0; }
+__device__ __forceinline__ int carried(const Carry& c) {
+  return c.partials != nullptr ? kCarryMaxChunks : 0;
+}
 
-// MODE 0: fused reduce + AdamW + working copy; 1: reduce only (g_out); 2:
-// AdamW only (g_in); 3: reduce to the bf16 wire format (wire_out); 4: reduce
-// with no output but the sums of squares.  In MODE 0 and 2 the gradient is
-// scaled by the clip coefficient when a.clip_total is set.  SUMSQ: per-piece
-// sums of squares of g (before clipping).
+// The segments of one unit: ti its tile, lo..hi the segments it overlaps
+// (lo > hi past the shard's end).
+struct UnitSegs {
+  TileInfo ti;
+  int lo, hi;
+};
+
+__device__ __forceinline__ UnitSegs unit_segs(const LayoutDev& L, const TileInfo& ti, int64_t u) {
+  UnitSegs s;
+  s.ti = ti;
+  s.lo = s.hi = s.ti.seg0;
+  if (s.ti.nseg > 1) {
+    const int64_t b = u * kUnit;
+    if (b >= L.n) {
+      s.lo = 1;
+      s.hi = 0;
+    } else {
+      const int64_t e = (b + kUnit < L.n ? b + kUnit : L.n) - 1;
+      s.lo = find_seg(L.seg_off, s.ti.seg0, s.ti.seg0 + s.ti.nseg - 1, b);
+      s.hi = find_seg(L.seg_off, s.lo, s.ti.seg0 + s.ti.nseg - 1, e);
+    }
+  }
+  return s;
+}
+
+// Segment of each element of a lane's vector, for a unit of several.
+__device__ __forceinline__ void lane_segs(const LayoutDev& L, const UnitSegs& us, int64_t base,
+                                          int cnt, int seg[8]) {
+  int s = cnt > 0 ? find_seg(L.seg_off, us.lo, us.hi, base) : us.lo;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (e < cnt)
+      while (base + e >= L.seg_off[s + 1]) ++s;
+    seg[e] = s;
+  }
+}
+
+// Sums of squares of unit u: one partial per (piece, unit) of its tile, the
+// exact double squares of a lane's 8 elements summed in order, then the wave
+// butterfly; 0 for the tile's segments that the unit does not touch.
+__device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us, int64_t u,
+                                           int lane, int cnt, const int seg[8],
+                                           const float g[8]) {
+  double* out = partials + (int64_t)us.ti.piece0 * kWaves + u % kWaves;
+  if (us.lo == us.hi) {
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) if (e < cnt) acc = acc + (double)g[e] * (double)g[e];
+    const double tot = wave_sum(acc);
+    if (lane == 0) out[(int64_t)(us.lo - us.ti.seg0) * kWaves] = tot;
+  } else {
+    for (int sj = us.lo; sj <= us.hi; ++sj) {
+      double acc = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (e < cnt && seg[e] == sj) acc = acc + (double)g[e] * (double)g[e];
+      const double tot = wave_sum(acc);
+      if (lane == 0) out[(int64_t)(sj - us.ti.seg0) * kWaves] = tot;
+    }
+  }
+  for (int j = lane; j < us.ti.nseg; j += 64)
+    if (us.ti.seg0 + j < us.lo || us.ti.seg0 + j > us.hi) out[(int64_t)j * kWaves] = 0.0;
+}
+
+// A streaming workgroup is one wave; its first unit (or group of units) and
+// its stride, behind the carriers.
+struct Place {
+  int lane;
+  int64_t at, stride;
+};
+
+__device__ __forceinline__ Place place(const Carry& c) {
+  const int64_t first = carried(c);
+  return {(int)threadIdx.x, blockIdx.x - first, (int64_t)gridDim.x - first};
+}
+
+// The AdamW step on the fp32 state, and the bf16 working copy.
+// MODE 0: fused with the reduction of the R peer gradients; 2: of the fp32
+// gradient g_in.  The gradient is scaled by the clip coefficient when
+// a.clip_total is set.  SUMSQ: per-piece sums of squares of g (before
+// clipping).
 template <int RT, int MODE, bool SUMSQ>
-__global__ void __launch_bounds__(kBlock) k_step(const StepArgs a) {
-  const int tid = threadIdx.x;
-  const bool clip = (MODE == 0 || MODE == 2) && a.clip_total != nullptr;
-  const float coef = clip ? clip_coef(a.clip_total, a.clip_max) : 1.0f;
+__global__ void __launch_bounds__(64) k_step(const StepArgs a) {
+  args_in<MODE == 2 ? 1 : RT == 0 ? 8 : RT>(a);
   if (run_carry(a.carry)) return;
-  const int cw = carried(a.carry);
-  for (int64_t t = blockIdx.x; t < a.L.n_tiles; t += (int64_t)gridDim.x - cw) {
-    const TileInfo ti = a.L.tiles[t];
-    const int64_t base = t * kTile + (int64_t)tid * kVec;
+  const Place w = place(a.carry);
+  const int lane = w.lane;
+  const int64_t n_units = a.L.n_tiles * kWaves;  // past n too: their partials are 0
+  for (int64_t u = w.at; u < n_units; u += w.stride) {
+    const int64_t base = u * kUnit + lane * kVec;
     const int64_t left = a.L.n - base;
     const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
 
-    // segment of each element (only needed where the tile straddles segments)
-    int seg[8];
-    if (ti.nseg > 1 && (SUMSQ || MODE == 0 || MODE == 2)) {
-      int s = cnt > 0 ? find_seg(a.L.seg_off, ti.seg0, ti.seg0 + ti.nseg - 1, base) : ti.seg0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (e < cnt)
-          while (base + e >= a.L.seg_off[s + 1]) ++s;
-        seg[e] = s;
-      }
-    }
+    // asked for before the streams, so that it is there when they are
+    i32x4 tile = ld_uniform(reinterpret_cast<const i32x4*>(a.L.tiles) + u / kWaves);
+    const bool clip = a.clip_total != nullptr;
+    double total =
+        ld_uniform(clip ? a.clip_total : reinterpret_cast<const double*>(a.L.tiles));
 
     float g[8];
     float p[8], m[8], v[8];
     if (cnt == kVec) {
-      if constexpr (MODE == 0 || MODE == 2) {
-        load_f32x8(a.master + base, p);
-        load_f32x8(a.m + base, m);
-        load_f32x8(a.v + base, v);
+      load_f32x8(a.master + base, p);
+      load_f32x8(a.m + base, m);
+      load_f32x8(a.v + base, v);
+      if constexpr (MODE == 2) {
+        load_f32x8(a.g_in + base, g);
+        loads_out();
+      } else {
+        reduce_vec<RT>(a, base, g);
       }
-      if constexpr (MODE == 2) load_f32x8(a.g_in + base, g);
-      else reduce_vec<RT>(a, base, g);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         p[e] = 0.f; m[e] = 0.f; v[e] = 0.f; g[e] = 0.f;
-        if constexpr (MODE == 0 || MODE == 2) {
-          if (e < cnt) { p[e] = a.master[base + e]; m[e] = a.m[base + e]; v[e] = a.v[base + e]; }
-        }
+        if (e < cnt) { p[e] = a.master[base + e]; m[e] = a.m[base + e]; v[e] = a.v[base + e]; }
         if constexpr (MODE == 2) {
           if (e < cnt) g[e] = a.g_in[base + e];
         }
@@ -315,132 +479,125 @@ __global__ void __launch_bounds__(kBlock) k_step(const StepArgs a) {
       }
     }
 
-    if constexpr (MODE == 4) {
-      // sums of squares only
-    } else if constexpr (MODE == 1) {
-      if (cnt == kVec) {
-        store_f32x8(a.g_out + base, g);
-      } else {
-        for (int e = 0; e < cnt; ++e) a.g_out[base + e] = g[e];
-      }
-    } else if constexpr (MODE == 3) {
-      if (cnt == kVec) {
-        st(reinterpret_cast<u32x4*>(a.wire_out + base), pack_bf16x8(g));
-      } else {
-        for (int e = 0; e < cnt; ++e) a.wire_out[base + e] = (uint16_t)to_bf16(g[e]);
-      }
-    } else {
-      const AdamScalars& s = a.s;
-      float gc[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) gc[e] = clip ? g[e] * coef : g[e];
-      float d[8];
-      if (ti.nseg == 1) {
-        const float du = ti.decay ? s.decay : 1.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] = du;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] = a.L.seg_decay[seg[e]] ? s.decay : 1.0f;
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float pe = p[e] * d[e];
-        const float mn = (s.b1 * m[e]) + (s.omb1 * gc[e]);
-        const float vn = (s.b2 * v[e]) + (s.omb2 * (gc[e] * gc[e]));
-        const float den = (__builtin_sqrtf(vn) / s.bc2_sqrt) + s.eps;
-        pe = pe - (s.step_size * (mn / den));
-        p[e] = pe; m[e] = mn; v[e] = vn;
-      }
-      if (cnt == kVec) {
-        store_f32x8(a.master + base, p);
-        store_f32x8(a.m + base, m);
-        store_f32x8(a.v + base, v);
-        if (MODE == 0 || a.working) st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(p));
-      } else {
-        for (int e = 0; e < cnt; ++e) {
-          a.master[base + e] = p[e];
-          a.m[base + e] = m[e];
-          a.v[base + e] = v[e];
-          if (MODE == 0 || a.working) a.working[base + e] = (uint16_t)to_bf16(p[e]);
-        }
-      }
-    }
+    // (not looked at before the streams' loads are out)
+    asm volatile("" : "+s"(tile), "+s"(total));
+    const TileInfo ti{tile.x, tile.y, tile.z, tile.w};
+    const UnitSegs us = unit_segs(a.L, ti, u);
+    int seg[8];
+    if (us.lo != us.hi) lane_segs(a.L, us, base, cnt, seg);
 
-    if constexpr (SUMSQ) {
-      // One partial per (piece, wave): the wave's share of the piece, the
-      // exact double squares of its 8 elements per lane summed in order, then
-      // the wave butterfly; no barrier.
-      const int wid = tid >> 6;
-      if (ti.nseg == 1) {
-        double acc = 0.0;
+    const AdamScalars& s = a.s;
+    const float coef = clip ? clip_coef(total, a.clip_max) : 1.0f;
+    float gc[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) if (e < cnt) acc = acc + (double)g[e] * (double)g[e];
-        const double tot = wave_sum(acc);
-        if ((tid & 63) == 0) a.partials[(int64_t)ti.piece0 * kWaves + wid] = tot;
-      } else {
-        for (int j = 0; j < ti.nseg; ++j) {
-          const int sj = ti.seg0 + j;
-          double acc = 0.0;
+    for (int e = 0; e < 8; ++e) gc[e] = clip ? g[e] * coef : g[e];
+    float d[8];
+    if (us.lo == us.hi) {
+      const int dec = us.ti.nseg == 1 ? us.ti.decay : (int)ld_uniform(a.L.seg_decay + us.lo);
+      const float du = dec ? s.decay : 1.0f;
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (e < cnt && seg[e] == sj) acc = acc + (double)g[e] * (double)g[e];
-          const double tot = wave_sum(acc);
-          if ((tid & 63) == 0) a.partials[((int64_t)ti.piece0 + j) * kWaves + wid] = tot;
-        }
+      for (int e = 0; e < 8; ++e) d[e] = du;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[e] = e < cnt && a.L.seg_decay[seg[e]] ? s.decay : 1.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float pe = p[e] * d[e];
+      const float mn = (s.b1 * m[e]) + (s.omb1 * gc[e]);
+      const float vn = (s.b2 * v[e]) + (s.omb2 * (gc[e] * gc[e]));
+      const float den = (__builtin_sqrtf(vn) / s.bc2_sqrt) + s.eps;
+      pe = pe - (s.step_size * (mn / den));
+      p[e] = pe; m[e] = mn; v[e] = vn;
+    }
+    if (cnt == kVec) {
+      store_f32x8(a.master + base, p);
+      store_f32x8(a.m + base, m);
+      store_f32x8(a.v + base, v);
+      if (MODE == 0 || a.working) st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(p));
+    } else {
+      for (int e = 0; e < cnt; ++e) {
+        a.master[base + e] = p[e];
+        a.m[base + e] = m[e];
+        a.v[base + e] = v[e];
+        if (MODE == 0 || a.working) a.working[base + e] = (uint16_t)to_bf16(p[e]);
       }
     }
+    if constexpr (SUMSQ) unit_sumsq(a.partials, us, u, lane, cnt, seg, g);
   }
 }
 
-// Reduction to the bf16 wire format with compile-time R (MODE 3 of k_step
-// for other R).  It needs no segment data, so it strides over 8-element
-// vectors and takes two per thread per iteration, issuing all 2R loads before
-// the arithmetic of either: a read-mostly pass needs that many loads in
-// flight to cover HBM latency at one workgroup per CU.  Same arithmetic and
-// bits as MODE 3.
-template <int RT>
-__global__ void __launch_bounds__(kBlock) k_wire(const StepArgs a) {
+// The reduction of the R peer gradients alone.  OUT 1: to fp32 (g_out); 3: to
+// the bf16 wire format (wire_out); 4: no output but the sums of squares.
+// SUMSQ: per-piece sums of squares of g.  A wave takes NV consecutive units of
+// a tile, all their loads issued first: a pass of few streams has too little
+// in flight per wave otherwise.
+template <int RT, int OUT, bool SUMSQ, int NV>
+__global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
   if (run_carry(a.carry)) return;
-  const int cw = carried(a.carry);
-  const int64_t nvec = (a.L.n + kVec - 1) / kVec;
-  const int64_t stride = ((int64_t)gridDim.x - cw) * kBlock;
-  for (int64_t v0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; v0 < nvec; v0 += 2 * stride) {
-    const int64_t v1 = v0 + stride;
-    const int64_t b0 = v0 * kVec, b1 = v1 * kVec;
-    if (b1 + kVec <= a.L.n) {  // both vectors full (b0 < b1)
-      u32x4 w0[RT], w1[RT];
-#pragma unroll
-      for (int r = 0; r < RT; ++r) w0[r] = ld_once(reinterpret_cast<const u32x4*>(a.grads[r] + b0));
-#pragma unroll
-      for (int r = 0; r < RT; ++r) w1[r] = ld_once(reinterpret_cast<const u32x4*>(a.grads[r] + b1));
-      float g0[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      float g1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int r = 0; r < RT; ++r) add_bf16x8(g0, w0[r]);
-#pragma unroll
-      for (int r = 0; r < RT; ++r) add_bf16x8(g1, w1[r]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        g0[e] = g0[e] * a.grad_scale;
-        g1[e] = g1[e] * a.grad_scale;
-      }
-      st(reinterpret_cast<u32x4*>(a.wire_out + b0), pack_bf16x8(g0));
-      st(reinterpret_cast<u32x4*>(a.wire_out + b1), pack_bf16x8(g1));
-      continue;
-    }
-    for (int k = 0; k < 2; ++k) {  // the last vectors of the shard
-      const int64_t vi = k == 0 ? v0 : v1;
-      if (vi >= nvec) break;
-      const int64_t base = vi * kVec;
-      const int64_t left = a.L.n - base;
-      float g[8];
-      if (left >= kVec) {
-        reduce_vec<RT>(a, base, g);
-        st(reinterpret_cast<u32x4*>(a.wire_out + base), pack_bf16x8(g));
+  const Place w = place(a.carry);
+  const int lane = w.lane;
+  const int64_t n_groups = a.L.n_tiles * (kWaves / NV);
+  for (int64_t b = w.at; b < n_groups; b += w.stride) {
+    const int64_t u0 = b * NV;
+    i32x4 tile{};
+    if constexpr (SUMSQ) tile = ld_uniform(reinterpret_cast<const i32x4*>(a.L.tiles) + u0 / kWaves);
+    float g[NV][8];
+    if ((u0 + NV) * kUnit <= a.L.n) {
+      if constexpr (NV == 1) {
+        reduce_vec<RT>(a, u0 * kUnit + lane * kVec, g[0]);
       } else {
-        reduce_tail(a, base, (int)left, g);
-        for (int e = 0; e < (int)left; ++e) a.wire_out[base + e] = (uint16_t)to_bf16(g[e]);
+        u32x4 x[NV][RT];
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+            x[i][r] = ld_once(reinterpret_cast<const u32x4*>(a.grads[r] + (u0 + i) * kUnit +
+                                                             lane * kVec));
+        loads_out();
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int r = 0; r < RT; ++r) add_bf16x8(acc, x[i][r]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) g[i][e] = acc[e] * a.grad_scale;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int64_t base = (u0 + i) * kUnit + lane * kVec;
+        const int64_t left = a.L.n - base;
+        if (left >= kVec) reduce_vec<RT>(a, base, g[i]);
+        else reduce_tail(a, base, left > 0 ? (int)left : 0, g[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int64_t base = (u0 + i) * kUnit + lane * kVec;
+      const int64_t left = a.L.n - base;
+      const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
+      if constexpr (OUT == 1) {
+        if (cnt == kVec) {
+          store_f32x8(a.g_out + base, g[i]);
+        } else {
+          for (int e = 0; e < cnt; ++e) a.g_out[base + e] = g[i][e];
+        }
+      } else if constexpr (OUT == 3) {
+        if (cnt == kVec) {
+          st(reinterpret_cast<u32x4*>(a.wire_out + base), pack_bf16x8(g[i]));
+        } else {
+          for (int e = 0; e < cnt; ++e) a.wire_out[base + e] = (uint16_t)to_bf16(g[i][e]);
+        }
+      }
+      if constexpr (SUMSQ) {
+        if (i == 0) asm volatile("" : "+s"(tile));
+        const TileInfo ti{tile.x, tile.y, tile.z, tile.w};
+        const UnitSegs us = unit_segs(a.L, ti, u0 + i);
+        int seg[8];
+        if (us.lo != us.hi) lane_segs(a.L, us, base, cnt, seg);
+        unit_sumsq(a.partials, us, u0 + i, lane, cnt, seg, g[i]);
       }
     }
   }
@@ -452,15 +609,14 @@ __global__ void __launch_bounds__(kBlock) k_wire(const StepArgs a) {
 //   d = nesterov ? delta + mu * buf : buf; p = prev - eta * d;
 //   master = prev = p; working = bf16(p).
 template <int GT, bool OUTER>
-__global__ void __launch_bounds__(kBlock) k_fedavg(const FedArgs a) {
+__global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
   if (run_carry(a.carry)) return;
-  const int cw = carried(a.carry);
-  const int64_t nvec = (a.n + kVec - 1) / kVec;
-  const int64_t stride = ((int64_t)gridDim.x - cw) * kBlock;
-  for (int64_t vi = (int64_t)blockIdx.x * kBlock + threadIdx.x; vi < nvec; vi += stride) {
-    const int64_t base = vi * kVec;
+  const Place w = place(a.carry);
+  const int64_t n_units = (a.n + kUnit - 1) / kUnit;
+  for (int64_t u = w.at; u < n_units; u += w.stride) {
+    const int64_t base = u * kUnit + w.lane * kVec;
     const int64_t left = a.n - base;
-    const int cnt = left >= kVec ? kVec : (int)left;
+    const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float prev[8], buf[8];
     if (cnt == kVec) {
@@ -468,24 +624,8 @@ __global__ void __launch_bounds__(kBlock) k_fedavg(const FedArgs a) {
         load_f32x8(a.prev + base, prev);
         load_f32x8(a.buf + base, buf);
       }
-      if constexpr (GT > 0) {
-        u32x4 w[GT];
-#pragma unroll
-        for (int k = 0; k < GT; ++k) w[k] = ld_once(reinterpret_cast<const u32x4*>(a.reps[k] + base));
-#pragma unroll
-        for (int k = 0; k < GT; ++k) fma_free_bf16x8(acc, a.w[k], w[k]);
-      } else {
-        constexpr int kChunk = 4;
-        for (int k0 = 0; k0 < a.G; k0 += kChunk) {
-          u32x4 w[kChunk];
-#pragma unroll
-          for (int k = 0; k < kChunk; ++k)
-            if (k0 + k < a.G) w[k] = ld_once(reinterpret_cast<const u32x4*>(a.reps[k0 + k] + base));
-#pragma unroll
-          for (int k = 0; k < kChunk; ++k)
-            if (k0 + k < a.G) fma_free_bf16x8(acc, a.w[k0 + k], w[k]);
-        }
-      }
+      sum_streams<GT>([&](int k) { return a.reps[k] + base; }, a.G,
+                      [&](int k, u32x4 w) { fma_free_bf16x8(acc, a.w[k], w); });
     } else {
       for (int e = 0; e < cnt; ++e) {
         float s = 0.f;
@@ -573,14 +713,13 @@ __global__ void __launch_bounds__(kBlock) k_total(const int64_t n_seg, const dou
 }
 
 // Broadcast receive: master = recv; working = bf16(recv).
-__global__ void __launch_bounds__(kBlock) k_bcast_recv(const BcastArgs a) {
+__global__ void __launch_bounds__(64) k_bcast_recv(const BcastArgs a) {
   if (run_carry(a.carry)) return;
-  const int cw = carried(a.carry);
+  const Place at = place(a.carry);
   const int64_t n = a.n;
-  const int64_t nvec = (n + kVec - 1) / kVec;
-  const int64_t stride = ((int64_t)gridDim.x - cw) * kBlock;
-  for (int64_t vi = (int64_t)blockIdx.x * kBlock + threadIdx.x; vi < nvec; vi += stride) {
-    const int64_t base = vi * kVec;
+  const int64_t n_units = (n + kUnit - 1) / kUnit;
+  for (int64_t ui = at.at; ui < n_units; ui += at.stride) {
+    const int64_t base = ui * kUnit + at.lane * kVec;
     const int64_t left = n - base;
     if (left >= kVec) {
       float x[8];
@@ -600,69 +739,97 @@ __global__ void __launch_bounds__(kBlock) k_bcast_recv(const BcastArgs a) {
   }
 }
 
-// grid workgroups for the stream, plus one for a carried finalize.
+// Workgroups as Shape says, behind the carriers of a carried finalize.
 template <typename Args>
-hipError_t launch(const void* fn, const Args& a, int grid, hipStream_t st) {
+hipError_t launch(const void* fn, const Args& a, Shape sh, hipStream_t st) {
   void* args[] = {const_cast<Args*>(&a)};
-  const unsigned g = (unsigned)grid + (a.carry.partials != nullptr ? 1u : 0u);
-  return hipLaunchKernel(fn, dim3(g), dim3(kBlock), args, 0, st);
+  const unsigned g = sh.grid + (a.carry.partials != nullptr ? (unsigned)kCarryMaxChunks : 0u);
+  return hipLaunchKernel(fn, dim3(g), dim3(64), args, sh.lds, st);
 }
 
-template <int MODE, bool SUMSQ>
-hipError_t dispatch_step(const StepArgs& a, int grid, hipStream_t st) {
+template <bool SUMSQ>
+hipError_t dispatch_step(const StepArgs& a, Shape sh, hipStream_t st) {
   switch (a.R) {
-    case 1: return launch((const void*)k_step<1, MODE, SUMSQ>, a, grid, st);
-    case 2: return launch((const void*)k_step<2, MODE, SUMSQ>, a, grid, st);
-    case 4: return launch((const void*)k_step<4, MODE, SUMSQ>, a, grid, st);
-    case 8: return launch((const void*)k_step<8, MODE, SUMSQ>, a, grid, st);
-    case 16: return launch((const void*)k_step<16, MODE, SUMSQ>, a, grid, st);
-    default: return launch((const void*)k_step<0, MODE, SUMSQ>, a, grid, st);
+    case 1: return launch((const void*)k_step<1, 0, SUMSQ>, a, sh, st);
+    case 2: return launch((const void*)k_step<2, 0, SUMSQ>, a, sh, st);
+    case 3: return launch((const void*)k_step<3, 0, SUMSQ>, a, sh, st);
+    case 4: return launch((const void*)k_step<4, 0, SUMSQ>, a, sh, st);
+    case 5: return launch((const void*)k_step<5, 0, SUMSQ>, a, sh, st);
+    case 6: return launch((const void*)k_step<6, 0, SUMSQ>, a, sh, st);
+    case 7: return launch((const void*)k_step<7, 0, SUMSQ>, a, sh, st);
+    case 8: return launch((const void*)k_step<8, 0, SUMSQ>, a, sh, st);
+    default: return launch((const void*)k_step<0, 0, SUMSQ>, a, sh, st);
+  }
+}
+
+// Several units per workgroup (sh.units) where the passes of one or two peers
+// ask for them.
+template <int RT, int OUT, bool SUMSQ>
+hipError_t reduce_units(const StepArgs& a, Shape sh, hipStream_t st) {
+  if constexpr (OUT == 4 && (RT == 1 || RT == 2)) {
+    if (sh.units == 4) return launch((const void*)k_reduce<RT, OUT, SUMSQ, 4>, a, sh, st);
+  }
+  if constexpr (OUT == 3 && RT == 1) {
+    if (sh.units == 2) return launch((const void*)k_reduce<RT, OUT, SUMSQ, 2>, a, sh, st);
+  }
+  if (sh.units != 1) return hipErrorInvalidValue;
+  return launch((const void*)k_reduce<RT, OUT, SUMSQ, 1>, a, sh, st);
+}
+
+template <int OUT, bool SUMSQ>
+hipError_t dispatch_reduce(const StepArgs& a, Shape sh, hipStream_t st) {
+  switch (a.R) {
+    case 1: return reduce_units<1, OUT, SUMSQ>(a, sh, st);
+    case 2: return reduce_units<2, OUT, SUMSQ>(a, sh, st);
+    case 3: return reduce_units<3, OUT, SUMSQ>(a, sh, st);
+    case 4: return reduce_units<4, OUT, SUMSQ>(a, sh, st);
+    case 5: return reduce_units<5, OUT, SUMSQ>(a, sh, st);
+    case 6: return reduce_units<6, OUT, SUMSQ>(a, sh, st);
+    case 7: return reduce_units<7, OUT, SUMSQ>(a, sh, st);
+    case 8: return reduce_units<8, OUT, SUMSQ>(a, sh, st);
+    default: return reduce_units<0, OUT, SUMSQ>(a, sh, st);
   }
 }
 
 }  // namespace
 
-hipError_t launch_local_step(const StepArgs& a, int grid, hipStream_t st) {
-  return a.partials ? dispatch_step<0, true>(a, grid, st) : dispatch_step<0, false>(a, grid, st);
+hipError_t launch_local_step(const StepArgs& a, Shape sh, hipStream_t st) {
+  return a.partials ? dispatch_step<true>(a, sh, st) : dispatch_step<false>(a, sh, st);
 }
 
-hipError_t launch_reduce(const StepArgs& a, int grid, hipStream_t st) {
-  return a.partials ? dispatch_step<1, true>(a, grid, st) : dispatch_step<1, false>(a, grid, st);
+hipError_t launch_reduce(const StepArgs& a, Shape sh, hipStream_t st) {
+  return a.partials ? dispatch_reduce<1, true>(a, sh, st) : dispatch_reduce<1, false>(a, sh, st);
 }
 
-hipError_t launch_reduce_wire(const StepArgs& a, int grid, hipStream_t st) {
-  switch (a.R) {
-    case 1: return launch((const void*)k_wire<1>, a, grid, st);
-    case 2: return launch((const void*)k_wire<2>, a, grid, st);
-    case 4: return launch((const void*)k_wire<4>, a, grid, st);
-    case 8: return launch((const void*)k_wire<8>, a, grid, st);
-    case 16: return launch((const void*)k_wire<16>, a, grid, st);
-    default: return dispatch_step<3, false>(a, grid, st);
-  }
+hipError_t launch_reduce_wire(const StepArgs& a, Shape sh, hipStream_t st) {
+  return dispatch_reduce<3, false>(a, sh, st);
 }
 
-hipError_t launch_bcast_recv(const BcastArgs& a, int grid, hipStream_t st) {
-  return launch((const void*)k_bcast_recv, a, grid, st);
+hipError_t launch_bcast_recv(const BcastArgs& a, Shape sh, hipStream_t st) {
+  return launch((const void*)k_bcast_recv, a, sh, st);
 }
 
-hipError_t launch_adamw(const StepArgs& a, int grid, hipStream_t st) {
-  return launch((const void*)k_step<1, 2, false>, a, grid, st);
+hipError_t launch_adamw(const StepArgs& a, Shape sh, hipStream_t st) {
+  return launch((const void*)k_step<1, 2, false>, a, sh, st);
 }
 
 template <bool OUTER>
-hipError_t dispatch_fedavg(const FedArgs& a, int grid, hipStream_t st) {
+hipError_t dispatch_fedavg(const FedArgs& a, Shape sh, hipStream_t st) {
   switch (a.G) {
-    case 1: return launch((const void*)k_fedavg<1, OUTER>, a, grid, st);
-    case 2: return launch((const void*)k_fedavg<2, OUTER>, a, grid, st);
-    case 4: return launch((const void*)k_fedavg<4, OUTER>, a, grid, st);
-    case 8: return launch((const void*)k_fedavg<8, OUTER>, a, grid, st);
-    case 16: return launch((const void*)k_fedavg<16, OUTER>, a, grid, st);
-    default: return launch((const void*)k_fedavg<0, OUTER>, a, grid, st);
+    case 1: return launch((const void*)k_fedavg<1, OUTER>, a, sh, st);
+    case 2: return launch((const void*)k_fedavg<2, OUTER>, a, sh, st);
+    case 3: return launch((const void*)k_fedavg<3, OUTER>, a, sh, st);
+    case 4: return launch((const void*)k_fedavg<4, OUTER>, a, sh, st);
+    case 5: return launch((const void*)k_fedavg<5, OUTER>, a, sh, st);
+    case 6: return launch((const void*)k_fedavg<6, OUTER>, a, sh, st);
+    case 7: return launch((const void*)k_fedavg<7, OUTER>, a, sh, st);
+    case 8: return launch((const void*)k_fedavg<8, OUTER>, a, sh, st);
+    default: return launch((const void*)k_fedavg<0, OUTER>, a, sh, st);
   }
 }
 
-hipError_t launch_fedavg(const FedArgs& a, int grid, hipStream_t st) {
-  return a.prev ? dispatch_fedavg<true>(a, grid, st) : dispatch_fedavg<false>(a, grid, st);
+hipError_t launch_fedavg(const FedArgs& a, Shape sh, hipStream_t st) {
+  return a.prev ? dispatch_fedavg<true>(a, sh, st) : dispatch_fedavg<false>(a, sh, st);
 }
 
 hipError_t launch_seg_finalize(const LayoutDev& L, const double* partials, double* chunk_sums,
@@ -699,8 +866,8 @@ hipError_t launch_zero_total(double* total, hipStream_t st) {
   return hipLaunchKernel((const void*)k_total, dim3(1), dim3(kBlock), a3, 0, st);
 }
 
-hipError_t launch_sumsq_only(const StepArgs& a, int grid, hipStream_t st) {
-  return dispatch_step<4, true>(a, grid, st);
+hipError_t launch_sumsq_only(const StepArgs& a, Shape sh, hipStream_t st) {
+  return dispatch_reduce<4, true>(a, sh, st);
 }
 
 hipError_t noalloc_scratch(int device, void** ptr) {
