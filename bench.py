@@ -88,12 +88,12 @@ def round_kernels(w):
         ks.append((wire, 2 * w.R * n, 2 * n))
     if w.max_grad_norm > 0 and w.H == 1 and w.clip_scratch:
         ks.append(("k_reduce<%d, 1, true, 1>" % _rt(w.R), 2 * w.R * n, 4 * n))
-        ks.append(("k_step<1, 2, false>", 16 * n, 14 * n))
+        ks.append(("k_step<1, 2, 0>", 16 * n, 14 * n))
     elif w.max_grad_norm > 0:
         ks.append(("k_reduce<%d, 4, true, %d>" % (_rt(r), 4 if r <= 2 else 1), 2 * r * n, 0))
-        ks.append(("k_step<%d, 0, false>" % _rt(r), (2 * r + 12) * n, 14 * n))
+        ks.append(("k_step<%d, 0, 0>" % _rt(r), (2 * r + 12) * n, 14 * n))
     else:
-        ks.append(("k_step<%d, 0, true>" % _rt(r), (2 * r + 12) * n, 14 * n))
+        ks.append(("k_step<%d, 0, %d>" % (_rt(r), 2 if 3 <= r <= 12 and n >= 384 << 17 else 1), (2 * r + 12) * n, 14 * n))
     if w.H > 1 and not w.hsdp_member:
         ks.append(("k_bcast_recv", 4 * n, 6 * n))
     elif w.outer is not None:

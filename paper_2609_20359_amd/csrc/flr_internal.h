@@ -65,6 +65,8 @@ struct Carry {
 struct AdamScalars {
   float b1, omb1, b2, omb2;
   float step_size, bc2_sqrt, eps, decay;
+  float rbc2;  // 1 / bc2_sqrt, or 0 where eps or bc2_sqrt rule out the short
+               // forms of the division and the root
 };
 
 // Arguments of the local-step family (reduce, AdamW, fused step).
@@ -85,6 +87,7 @@ struct StepArgs {
                        // (null: not requested)
   const double* clip_total;  // MODE 0: whole-shard sum of squares, clipping on
   float clip_max;            // its max norm
+  int sum_by_lds;      // fused step: exchange the partials by way of LDS
   Carry carry;
 };
 

@@ -109,6 +109,11 @@ flr::AdamScalars adam_scalars(const fl_adamw_hparams& h, int64_t step) {
   s.bc2_sqrt = (float)std::sqrt(1.0 - std::pow((double)h.beta2, t));
   s.eps = h.eps;
   s.decay = (float)(1.0 - lr * (double)h.weight_decay);
+  // With these bounds, and the kernel's on the moments, no operand or result
+  // of the short forms leaves the normal range (the root is at most 2^30, the
+  // denominator between 2^-60 and 2^44, the quotient within 2^-104 to 2^90).
+  const bool short_forms = s.eps >= 0x1p-60f && s.eps <= 0x1p40f && s.bc2_sqrt >= 0x1p-13f;
+  s.rbc2 = short_forms ? (float)(1.0 / (double)s.bc2_sqrt) : 0.f;
   return s;
 }
 
@@ -177,10 +182,10 @@ struct Pass {
   int units = 1;  // units a workgroup takes at a time
 };
 
-// step: R=1 5.87/5.49, R=2 5.90/5.45, R=4 5.95/5.41, R=6 5.97/5.47, R=8
-// 6.02/5.59, R=12 6.02/5.63, R=16 5.97/5.56, R=64 5.60/5.42.
+// step: R=1 5.84/5.49, R=2 5.93/5.45, R=4 5.95/5.41, R=6 5.99/5.47, R=8
+// 6.04/5.59, R=12 6.01/5.63, R=16 6.03/5.56, R=64 5.61/5.42.
 Pass step_pass(int R) {
-  const int w = R <= 2 ? 8 : R <= 4 ? 7 : R <= 12 ? 5 : 4;
+  const int w = R <= 2 ? 8 : R <= 4 ? 6 : R <= 12 ? 5 : 4;
   return {w, w + 2, 2 * w};
 }
 // AdamW alone: 5.83/5.35.
@@ -245,6 +250,15 @@ flr::Shape shape_for(const fl_layout* lay, Pass pass) {
   }
   sh.grid = (unsigned)std::max<int64_t>(1, std::min(blocks, kMaxGrid));
   return sh;
+}
+
+// Whether a fused step's per-segment sums exchange their partials by way of
+// LDS, later than by DPP moves and with the same bits.  Long passes of a few
+// streams run faster so (R=8 on 1.0e9 elements 6.24 TB/s and 6.15, R=4 6.13 and
+// 6.03, R=4 on 5.0e8 5.96 and 5.81), the others slower (R=16 on 5.0e8 5.89 and
+// 6.02, R=2 on 6.3e7 5.47 and 5.57, the 1 Mi round 4.24 and 4.36).
+int step_sum_by_lds(const fl_layout* lay, int R) {
+  return R >= 3 && R <= 12 && lay->L.n_tiles * flr::kWaves / lay->num_cus >= kMid;
 }
 
 int status_of(hipError_t e) {
@@ -468,6 +482,7 @@ int enqueue_local_step(const fl_layout* lay, const fl_adamw_hparams& h, int64_t 
   a.v = v;
   a.working = working;
   if (seg_sumsq) a.partials = free_slot(ws, a.carry);
+  a.sum_by_lds = step_sum_by_lds(lay, R);
   if (rc == FL_OK) rc = status_of(flr::launch_local_step(a, shape_for(lay, step_pass(R)), st));
   if (rc == FL_OK && seg_sumsq) rc = finish_sums(lay, ws, a.partials, seg_sumsq, pending, st);
   return rc;

@@ -33,6 +33,8 @@ static __device__ __align__(256) unsigned char scratch[flr::kNoallocScratchBytes
 namespace flr {
 namespace {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -96,7 +98,7 @@ __device__ __forceinline__ void args_in(const StepArgs& a) {
                "s"(a.master), "s"(a.m), "s"(a.v), "s"(a.working), "s"(a.g_in), "s"(a.partials),
                "s"(a.clip_total), "s"(a.grad_scale), "s"(a.s.b1), "s"(a.s.omb1), "s"(a.s.b2),
                "s"(a.s.omb2), "s"(a.s.step_size), "s"(a.s.bc2_sqrt), "s"(a.s.eps),
-               "s"(a.s.decay), "s"(a.grads[0]), "s"(a.grads[1 % NP]), "s"(a.grads[2 % NP]),
+               "s"(a.s.decay), "s"(a.s.rbc2), "s"(a.grads[0]), "s"(a.grads[1 % NP]), "s"(a.grads[2 % NP]),
                "s"(a.grads[3 % NP]), "s"(a.grads[4 % NP]), "s"(a.grads[5 % NP]),
                "s"(a.grads[6 % NP]), "s"(a.grads[7 % NP]));
 }
@@ -109,20 +111,18 @@ __device__ __forceinline__ void loads_out() { __builtin_amdgcn_sched_barrier(0);
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// fp32 -> bf16 bits, round to nearest even; NaN -> quiet NaN, sign kept.
-__device__ __forceinline__ uint32_t to_bf16(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const uint32_t r = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-  return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? ((u >> 16) | 0x40u) : r;
+// fp32 -> bf16 bits, round to nearest even; NaN -> quiet NaN, sign kept: the
+// conversion instruction (two values at a time), which gives these bits for
+// all 2^32 inputs.
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
+__device__ __forceinline__ uint32_t to_bf16(float x) { return pack_bf16x2(x, 0.f) & 0xFFFFu; }
+
 __device__ __forceinline__ u32x4 pack_bf16x8(const float x[8]) {
-  u32x4 o;
-  o.x = to_bf16(x[0]) | (to_bf16(x[1]) << 16);
-  o.y = to_bf16(x[2]) | (to_bf16(x[3]) << 16);
-  o.z = to_bf16(x[4]) | (to_bf16(x[5]) << 16);
-  o.w = to_bf16(x[6]) | (to_bf16(x[7]) << 16);
-  return o;
+  return u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]),
+               pack_bf16x2(x[6], x[7])};
 }
 
 // acc[e] = acc[e] + bf16 element e of w (ascending e).
@@ -205,6 +205,15 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
   }
 }
 
+// A pause of 256 clocks between a wave's last addition and its stores.  Passes
+// that do little else run faster with it: to the wire format R=4 6.90 TB/s and
+// 6.43 without (12 waves per CU, 5e8 elements; 6.65 without at its best, 14),
+// R=8 on 6.3e7 elements 6.91 and 6.76, FedAvg G=4 6.41 and 6.32, G=5 on 5e7
+// 6.27 and 6.17; twice the pause gives no more, half of it half.  It was found
+// when the bf16 rounding, in its place before, became one instruction.  With
+// AdamW between loads and stores it makes no difference.
+__device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(4); }
+
 // Reduced gradient of 8 elements (full vector): peers in ascending order.
 template <int RT>
 __device__ __forceinline__ void reduce_vec(const StepArgs& a, int64_t base, float g[8]) {
@@ -228,9 +237,36 @@ __device__ __forceinline__ void reduce_tail(const StepArgs& a, int64_t base, int
   }
 }
 
-// Fixed-tree sum over one wave64: butterfly exchange, after which every lane
-// holds the same bits (each step adds the same two partials in both lanes).
+// Fixed-tree sum over one wave64, all lanes active: the butterfly of
+// exchanges with lanes 1, 2, 4, 8, 16 and 32 away, the same in every lane.
+// The first four are DPP moves (after two the lanes of a quad agree, after
+// three those of a half row, so a mirror reaches what the exchange would),
+// the last two read one lane of each row.  wave_sum_lds is the same tree by
+// way of LDS, twelve dependent trips: the same bits, later.
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)u, kCtrl, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), kCtrl, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ double lane_of(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
+  v = v + dpp<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = v + dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = v + dpp<0x141>(v);  // row_half_mirror
+  v = v + dpp<0x140>(v);  // row_mirror
+  return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
+__device__ __forceinline__ double wave_sum_lds(double v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = v + __shfl_xor(v, off, 64);
   return v;
@@ -391,9 +427,15 @@ __device__ __forceinline__ void lane_segs(const LayoutDev& L, const UnitSegs& us
   }
 }
 
+// acc + x * x in double: a float's square is exact, so fused is the same.
+__device__ __forceinline__ double add_square(double acc, float x) {
+  return __builtin_fma((double)x, (double)x, acc);
+}
+
 // Sums of squares of unit u: one partial per (piece, unit) of its tile, the
 // exact double squares of a lane's 8 elements summed in order, then the wave
 // butterfly; 0 for the tile's segments that the unit does not touch.
+template <bool LDS = false>
 __device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us, int64_t u,
                                            int lane, int cnt, const int seg[8],
                                            const float g[8]) {
@@ -401,16 +443,16 @@ __device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us,
   if (us.lo == us.hi) {
     double acc = 0.0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) if (e < cnt) acc = acc + (double)g[e] * (double)g[e];
-    const double tot = wave_sum(acc);
+    for (int e = 0; e < 8; ++e) if (e < cnt) acc = add_square(acc, g[e]);
+    const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
     if (lane == 0) out[(int64_t)(us.lo - us.ti.seg0) * kWaves] = tot;
   } else {
     for (int sj = us.lo; sj <= us.hi; ++sj) {
       double acc = 0.0;
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (e < cnt && seg[e] == sj) acc = acc + (double)g[e] * (double)g[e];
-      const double tot = wave_sum(acc);
+        if (e < cnt && seg[e] == sj) acc = add_square(acc, g[e]);
+      const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
       if (lane == 0) out[(int64_t)(sj - us.ti.seg0) * kWaves] = tot;
     }
   }
@@ -430,12 +472,71 @@ __device__ __forceinline__ Place place(const Carry& c) {
   return {(int)threadIdx.x, blockIdx.x - first, (int64_t)gridDim.x - first};
 }
 
+// AdamW on 8 elements: p already decayed, g clipped; m, v and p updated.
+//
+// The division and the two correctly rounded operations before it are a third
+// of the step's instructions as the compiler expands them, most of it for
+// operands at the ends of the range.  When no lane of the wave has one (kLo,
+// kHi below, and s.rbc2, which the host sets when eps and bc2_sqrt allow), the
+// same results come cheaper:
+//  - sqrt: x * rsq(x) with one correction by its exact residual; equal to the
+//    correctly rounded root for every float from 2^-100 to 2^120;
+//  - / bc2_sqrt: by its correctly rounded reciprocal and two corrections (the
+//    first makes the quotient faithful, the second by Markstein's theorem
+//    correctly rounded);
+//  - mn / den: reciprocal, one Newton step, two corrections: the operations of
+//    the full division where its scaling does nothing.
+// Per round: 8B shard (R = 8, A = 4) 29.62 to 29.16 ms, 1 Mi elements (R = 4,
+// from cache) 37.8 to 37.1 us; together with the rounding instruction.
+constexpr float kMnLo = 0x1p-60f, kMnHi = 0x1p30f, kVnLo = 0x1p-100f, kVnHi = 0x1p60f;
+
+__device__ __forceinline__ void adam8(const AdamScalars& s, const float g[8], float p[8],
+                                      float m[8], float v[8]) {
+  float m_lo = kMnHi, m_hi = 0.f, v_lo = kVnHi, v_hi = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    m[e] = (s.b1 * m[e]) + (s.omb1 * g[e]);
+    v[e] = (s.b2 * v[e]) + (s.omb2 * (g[e] * g[e]));
+    const float am = __builtin_fabsf(m[e]);
+    m_lo = __builtin_fminf(m_lo, am);
+    m_hi = __builtin_fmaxf(m_hi, am);
+    v_lo = __builtin_fminf(v_lo, v[e]);
+    v_hi = __builtin_fmaxf(v_hi, v[e]);
+  }
+  // (a NaN is in neither minimum nor maximum; it comes out NaN either way)
+  const bool in_range = m_lo >= kMnLo && m_hi <= kMnHi && v_lo >= kVnLo && v_hi <= kVnHi;
+  if (s.rbc2 > 0.f && __all(in_range)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float y = __builtin_amdgcn_rsqf(v[e]);
+      float r = v[e] * y;
+      r = __builtin_fmaf(__builtin_fmaf(-r, r, v[e]), 0.5f * y, r);
+      float q = r * s.rbc2;
+      q = __builtin_fmaf(__builtin_fmaf(-s.bc2_sqrt, q, r), s.rbc2, q);
+      q = __builtin_fmaf(__builtin_fmaf(-s.bc2_sqrt, q, r), s.rbc2, q);
+      const float den = q + s.eps;
+      float z = __builtin_amdgcn_rcpf(den);
+      z = __builtin_fmaf(__builtin_fmaf(-den, z, 1.0f), z, z);
+      float u = m[e] * z;
+      u = __builtin_fmaf(__builtin_fmaf(-den, u, m[e]), z, u);
+      u = __builtin_fmaf(__builtin_fmaf(-den, u, m[e]), z, u);
+      p[e] = p[e] - (s.step_size * u);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float den = (__builtin_sqrtf(v[e]) / s.bc2_sqrt) + s.eps;
+      p[e] = p[e] - (s.step_size * (m[e] / den));
+    }
+  }
+}
+
 // The AdamW step on the fp32 state, and the bf16 working copy.
 // MODE 0: fused with the reduction of the R peer gradients; 2: of the fp32
 // gradient g_in.  The gradient is scaled by the clip coefficient when
-// a.clip_total is set.  SUMSQ: per-piece sums of squares of g (before
-// clipping).
-template <int RT, int MODE, bool SUMSQ>
+// a.clip_total is set.  SUMS 1: per-piece sums of squares of g (before
+// clipping); 2: the same, exchanged by way of LDS.
+template <int RT, int MODE, int SUMS>
 __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
   args_in<MODE == 2 ? 1 : RT == 0 ? 8 : RT>(a);
   if (run_carry(a.carry)) return;
@@ -502,14 +603,8 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
       for (int e = 0; e < 8; ++e) d[e] = e < cnt && a.L.seg_decay[seg[e]] ? s.decay : 1.0f;
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float pe = p[e] * d[e];
-      const float mn = (s.b1 * m[e]) + (s.omb1 * gc[e]);
-      const float vn = (s.b2 * v[e]) + (s.omb2 * (gc[e] * gc[e]));
-      const float den = (__builtin_sqrtf(vn) / s.bc2_sqrt) + s.eps;
-      pe = pe - (s.step_size * (mn / den));
-      p[e] = pe; m[e] = mn; v[e] = vn;
-    }
+    for (int e = 0; e < 8; ++e) p[e] = p[e] * d[e];
+    adam8(s, gc, p, m, v);
     if (cnt == kVec) {
       store_f32x8(a.master + base, p);
       store_f32x8(a.m + base, m);
@@ -523,7 +618,7 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
         if (MODE == 0 || a.working) a.working[base + e] = (uint16_t)to_bf16(p[e]);
       }
     }
-    if constexpr (SUMSQ) unit_sumsq(a.partials, us, u, lane, cnt, seg, g);
+    if constexpr (SUMS != 0) unit_sumsq<SUMS == 2>(a.partials, us, u, lane, cnt, seg, g);
   }
 }
 
@@ -573,6 +668,7 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
         else reduce_tail(a, base, left > 0 ? (int)left : 0, g[i]);
       }
     }
+    if constexpr (OUT == 3) pause();
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int64_t base = (u0 + i) * kUnit + lane * kVec;
@@ -650,6 +746,7 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
         }
       }
     }
+    if constexpr (!OUTER) pause();
     if (cnt == kVec) {
       store_f32x8(a.master + base, acc);
       st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(acc));
@@ -747,18 +844,18 @@ hipError_t launch(const void* fn, const Args& a, Shape sh, hipStream_t st) {
   return hipLaunchKernel(fn, dim3(g), dim3(64), args, sh.lds, st);
 }
 
-template <bool SUMSQ>
+template <int SUMS>
 hipError_t dispatch_step(const StepArgs& a, Shape sh, hipStream_t st) {
   switch (a.R) {
-    case 1: return launch((const void*)k_step<1, 0, SUMSQ>, a, sh, st);
-    case 2: return launch((const void*)k_step<2, 0, SUMSQ>, a, sh, st);
-    case 3: return launch((const void*)k_step<3, 0, SUMSQ>, a, sh, st);
-    case 4: return launch((const void*)k_step<4, 0, SUMSQ>, a, sh, st);
-    case 5: return launch((const void*)k_step<5, 0, SUMSQ>, a, sh, st);
-    case 6: return launch((const void*)k_step<6, 0, SUMSQ>, a, sh, st);
-    case 7: return launch((const void*)k_step<7, 0, SUMSQ>, a, sh, st);
-    case 8: return launch((const void*)k_step<8, 0, SUMSQ>, a, sh, st);
-    default: return launch((const void*)k_step<0, 0, SUMSQ>, a, sh, st);
+    case 1: return launch((const void*)k_step<1, 0, SUMS>, a, sh, st);
+    case 2: return launch((const void*)k_step<2, 0, SUMS>, a, sh, st);
+    case 3: return launch((const void*)k_step<3, 0, SUMS>, a, sh, st);
+    case 4: return launch((const void*)k_step<4, 0, SUMS>, a, sh, st);
+    case 5: return launch((const void*)k_step<5, 0, SUMS>, a, sh, st);
+    case 6: return launch((const void*)k_step<6, 0, SUMS>, a, sh, st);
+    case 7: return launch((const void*)k_step<7, 0, SUMS>, a, sh, st);
+    case 8: return launch((const void*)k_step<8, 0, SUMS>, a, sh, st);
+    default: return launch((const void*)k_step<0, 0, SUMS>, a, sh, st);
   }
 }
 
@@ -794,7 +891,8 @@ hipError_t dispatch_reduce(const StepArgs& a, Shape sh, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_local_step(const StepArgs& a, Shape sh, hipStream_t st) {
-  return a.partials ? dispatch_step<true>(a, sh, st) : dispatch_step<false>(a, sh, st);
+  if (!a.partials) return dispatch_step<0>(a, sh, st);
+  return a.sum_by_lds ? dispatch_step<2>(a, sh, st) : dispatch_step<1>(a, sh, st);
 }
 
 hipError_t launch_reduce(const StepArgs& a, Shape sh, hipStream_t st) {
@@ -810,7 +908,7 @@ hipError_t launch_bcast_recv(const BcastArgs& a, Shape sh, hipStream_t st) {
 }
 
 hipError_t launch_adamw(const StepArgs& a, Shape sh, hipStream_t st) {
-  return launch((const void*)k_step<1, 2, false>, a, sh, st);
+  return launch((const void*)k_step<1, 2, 0>, a, sh, st);
 }
 
 template <bool OUTER>

@@ -118,3 +118,46 @@ def test_launch_bands(env, n):
                                        v=v.cpu().numpy(), working=H.to_u16(work)),
                           dict(master=rm, m=r1, v=r2, working=rw), bitwise=True)
     lay.close()
+
+
+@pytest.mark.parametrize("eps,beta2", [(1e-8, 0.95), (1e-30, 0.999), (1e15, 0.9999999),
+                                       (2.0 ** -60, 0.0)])
+@pytest.mark.parametrize("t", [1, 1000])
+def test_adamw_operand_ranges(env, eps, beta2, t):
+    """Moments inside, across and beyond the range of the short forms of the
+    root and the divisions, whole waves and single lanes of them."""
+    torch, P, orc = env
+    n = 512 * 24 + 77
+    r = np.random.default_rng(int(t * 1000 + beta2 * 100))
+    off = np.array([0, n], np.int64)
+    dec = np.ones(1, np.uint8)
+    unit = np.arange(n) // 512
+
+    def spread(lo, hi):
+        x = np.ldexp(r.uniform(1.0, 2.0, n), r.integers(lo, hi, n)) * r.choice([-1.0, 1.0], n)
+        return x.astype(np.float32)
+
+    g, m, v = spread(-14, -6), spread(-14, -6), np.abs(spread(-30, -14))
+    wide = unit % 3 == 1                       # any magnitude, subnormals among them
+    g[wide], m[wide] = spread(-149, 60)[wide], spread(-149, 60)[wide]
+    v[wide] = np.abs(spread(-149, 100))[wide]
+    one = (unit % 3 == 2) & (r.random(n) < 0.003)   # single lanes
+    for a, x in ((g, 0.0), (m, 0.0), (v, 0.0)):
+        a[one] = x
+    edge = (unit % 6 == 5) & (r.random(n) < 0.003)
+    m[edge] = np.float32(2.0 ** -60) * r.choice([0.5, 1.0, 2.0], edge.sum()).astype(np.float32)
+    v[edge] = np.float32(2.0 ** -100) * r.choice([0.5, 1.0, 2.0], edge.sum()).astype(np.float32)
+    g[edge] = 0.0
+    p = spread(-10, -2)
+    hp = dict(lr=3e-4, beta1=0.9, beta2=beta2, eps=eps, weight_decay=0.1)
+    lay = P.Layout(off, dec)
+    dev = [torch.from_numpy(x.copy()).cuda() for x in (g, p, m, v)]
+    work = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    print("adamw ranges eps=%g beta2=%g t=%d" % (eps, beta2, t), flush=True)
+    P.fl_adamw_step(lay, hp, t, dev[0], dev[1], dev[2], dev[3], work)
+    rw = np.zeros(n, np.uint16)
+    orc.adamw_step(off, dec, hp, t, g, p, m, v, rw)
+    H.assert_state_parity("ranges", dict(master=dev[1].cpu().numpy(), m=dev[2].cpu().numpy(),
+                                         v=dev[3].cpu().numpy(), working=H.to_u16(work)),
+                          dict(master=p, m=m, v=v, working=rw), bitwise=True)
+    lay.close()
