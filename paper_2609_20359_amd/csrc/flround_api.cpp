@@ -664,7 +664,8 @@ int fl_layout_create(int64_t n, int64_t n_seg, const int64_t* seg_offsets,
   }
   if (b_ws) {
     e = hipMemset(static_cast<char*>(mem) + b_tables, 0, b_ws);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&lay->ws_done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(
+          &lay->ws_done, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) {
       (void)hipFree(mem);
       delete lay;
