@@ -156,6 +156,13 @@ def _buf(t, n, esize, what):
         return None
     if isinstance(t, int):
         return t
+    try:
+        if (t.is_cuda and t.is_contiguous() and t.element_size() == esize
+                and t.numel() == n):
+            return t.data_ptr()
+    except AttributeError:
+        pass
+    # something is wrong with it: say what
     if not getattr(t, "is_cuda", False):
         raise ValueError("%s must be a CUDA tensor" % what)
     if not t.is_contiguous():
@@ -180,6 +187,21 @@ def _bufs(ts, count, n, esize, what):
         size = count
     else:
         size = max(len(ts), 1)
+    ptrs = []
+    try:
+        for t in ts:
+            if t is None:
+                ptrs.append(None)
+            elif (t.is_cuda and t.is_contiguous() and t.element_size() == esize
+                  and t.numel() == n):
+                ptrs.append(t.data_ptr())
+            else:
+                break
+        else:
+            return (ctypes.c_void_p * size)(*ptrs)
+    except AttributeError:
+        pass
+    # raw addresses among them, or something wrong: one by one
     arr = (ctypes.c_void_p * size)()
     for i, t in enumerate(ts):
         arr[i] = _buf(t, n, esize, "%s[%d]" % (what, i))
@@ -193,12 +215,25 @@ def _host_list(xs, count, ctype, what):
     return (ctype * max(count, 1))(*xs)
 
 
+_raw_stream = None   # (current device) -> its current stream's hipStream_t
+
+
 def _stream(stream):
     if stream is not None:
         return ctypes.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
-    import torch
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
 
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the current stream as a number: 0.3 us, against 2.9 us by way of a
+        # torch.cuda.Stream object, which a call of a few us would spend on it
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        dev = torch.cuda.current_device
+        if raw is not None:
+            _raw_stream = lambda: raw(dev())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    return ctypes.c_void_p(_raw_stream())
 
 
 def hparams(hp):
