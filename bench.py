@@ -128,7 +128,7 @@ def summarize_pmc(fetch_csv, write_csv, copy_mib, cmd_fetch, cmd_write, workload
 
     def pick(table, name):
         """Mean and count over every dispatch of the kernel (all grid sizes:
-        a pass that carries the previous finalize has one more workgroup)."""
+        a pass that carries the previous finalize has eight more workgroups)."""
         hits = [v for (k, g), v in table.items() if name in k]
         if not hits:
             raise KeyError(name)
@@ -193,8 +193,8 @@ PROBE_FILES = {1003782144: os.path.join(ROOT, "profiles", "hbm_probe_reference_l
 
 
 def probe_reference(w, achieved):
-    """The rate of the local step's access pattern with no arithmetic, in the
-    library's loop and launch structure (a same-design reference, not a
+    """The rate of the local step's access pattern with no arithmetic, in
+    a grid-stride loop of resident workgroups (a reference, not a
     bound), from the committed probe summary for this shard length, where the
     probe measured the pattern (a plain fused step: one replica, no
     clipping); else None."""
