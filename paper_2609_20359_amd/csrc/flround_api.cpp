@@ -212,16 +212,17 @@ Pass wire_pass(int R) {
   const int w = R == 2 ? 32 : R == 3 ? 16 : R <= 5 ? 12 : R == 6 ? 9 : R <= 8 ? 7 : 6;
   return {w, w, 2 * w};
 }
-// FedAvg: G=1 5.64/3.58, G=2 6.02/4.23, G=4 6.40/5.83, G=5 6.45/6.06, G=8
-// 6.62/6.05, G=16 6.26/5.87.  With the outer step: G=2 5.66/5.24, G=4
-// 5.65/5.32, G=8 5.97/5.39.
+// FedAvg: G=1 6.52/5.9, G=2 6.58/6.3, G=4 6.70/6.4, G=5 6.71/6.5, G=8 6.56/6.0,
+// G=16 6.23/5.9 (16 waves for the second figure from G=4 on).  With the outer
+// step: G=4 6.12/5.4, G=8 6.05/5.5, G=16 6.12/5.7.
 Pass fedavg_pass(int G, bool outer) {
-  const int w = outer ? 5 : G == 1 ? 14 : G == 2 ? 10 : G <= 4 ? 9 : G <= 5 ? 8 : G <= 7 ? 7
+  const int w = outer ? (G <= 6 ? 5 : 4)
+                : G == 1 ? 16 : G == 2 ? 14 : G == 3 ? 12 : G <= 5 ? 10 : G <= 6 ? 9 : G <= 8 ? 7
               : G <= 12 ? 6 : 5;
   return {w, w, 2 * w};
 }
-// Broadcast receive: 5.49/3.98.
-constexpr Pass kBcastPass = {12, 12, 12};
+// Broadcast receive: 6.62/6.47 (16 waves).
+constexpr Pass kBcastPass = {10, 12, 12};
 
 // Shorter passes gain from more waves, as the ramps at both ends count for
 // more and the window for less: the step at R = 8 on 27e6 elements runs at

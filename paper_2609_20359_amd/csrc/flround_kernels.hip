@@ -37,6 +37,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -149,16 +150,44 @@ __device__ __forceinline__ void fma_free_bf16x8(float acc[8], float wt, u32x4 w)
   acc[7] = acc[7] + (wt * bf16_hi(w.w));
 }
 
+// Where a lane's 8 elements lie.  kWhole: 8 in a row, one 16-byte access per
+// bf16 stream and two of fp32, each of which covers every other 16 bytes of the
+// wave's lines.  kHalves: elements 4l .. 4l + 3 of each half of the unit, so
+// that one fp32 access covers whole lines.  Passes that read little for what
+// they write run on halves: whole, their lines left the L2 half written
+// (broadcast receive 1.12 of its bytes written, FedAvg G=4 1.03).
+constexpr int kWhole = 4, kHalves = kUnit / 2;  // distance of the second four
+
+template <int kGap = kWhole>
 __device__ __forceinline__ void load_f32x8(const float* p, float x[8]) {
   const f32x4 a = ld(reinterpret_cast<const f32x4*>(p));
-  const f32x4 b = ld(reinterpret_cast<const f32x4*>(p + 4));
+  const f32x4 b = ld(reinterpret_cast<const f32x4*>(p + kGap));
   x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
   x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
+template <int kGap = kWhole>
 __device__ __forceinline__ void store_f32x8(float* p, const float x[8]) {
   st(reinterpret_cast<f32x4*>(p), f32x4{x[0], x[1], x[2], x[3]});
-  st(reinterpret_cast<f32x4*>(p + 4), f32x4{x[4], x[5], x[6], x[7]});
+  st(reinterpret_cast<f32x4*>(p + kGap), f32x4{x[4], x[5], x[6], x[7]});
+}
+
+template <int kGap>
+__device__ __forceinline__ u32x4 load_bf16x8(const uint16_t* p) {
+  if constexpr (kGap == kWhole) {
+    return ld_once(reinterpret_cast<const u32x4*>(p));
+  } else {
+    const u32x2 a = ld_once(reinterpret_cast<const u32x2*>(p));
+    const u32x2 b = ld_once(reinterpret_cast<const u32x2*>(p + kGap));
+    return u32x4{a.x, a.y, b.x, b.y};
+  }
+}
+
+// (on halves)
+__device__ __forceinline__ void store_bf16_halves(uint16_t* p, const float x[8]) {
+  const u32x4 w = pack_bf16x8(x);
+  st(reinterpret_cast<u32x2*>(p), u32x2{w.x, w.y});
+  st(reinterpret_cast<u32x2*>(p + kHalves), u32x2{w.z, w.w});
 }
 
 // Sum over n bf16 streams of element e of a full vector, streams in ascending
@@ -167,24 +196,24 @@ __device__ __forceinline__ void store_f32x8(float* p, const float x[8]) {
 // at a time, the next chunk's loads issued before this one's additions.
 constexpr int kChunk = 8;
 
-template <int N, typename Ptr, typename Add>
+template <int N, int kGap = kWhole, typename Ptr, typename Add>
 __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
   if constexpr (N > 0) {
     u32x4 w[N];
 #pragma unroll
-    for (int k = 0; k < N; ++k) w[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k)));
+    for (int k = 0; k < N; ++k) w[k] = load_bf16x8<kGap>(ptr(k));
     loads_out();
 #pragma unroll
     for (int k = 0; k < N; ++k) add(k, w[k]);
   } else {
     u32x4 w[kChunk];
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) w[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k)));
+    for (int k = 0; k < kChunk; ++k) w[k] = load_bf16x8<kGap>(ptr(k));
     int k0 = kChunk;
     for (; k0 + kChunk <= n; k0 += kChunk) {
       u32x4 x[kChunk];
 #pragma unroll
-      for (int k = 0; k < kChunk; ++k) x[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k0 + k)));
+      for (int k = 0; k < kChunk; ++k) x[k] = load_bf16x8<kGap>(ptr(k0 + k));
       loads_out();
 #pragma unroll
       for (int k = 0; k < kChunk; ++k) {
@@ -195,7 +224,7 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
     u32x4 x[kChunk];
 #pragma unroll
     for (int k = 0; k < kChunk - 1; ++k)
-      if (k0 + k < n) x[k] = ld_once(reinterpret_cast<const u32x4*>(ptr(k0 + k)));
+      if (k0 + k < n) x[k] = load_bf16x8<kGap>(ptr(k0 + k));
     loads_out();
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) add(k0 - kChunk + k, w[k]);
@@ -710,57 +739,60 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
   const Place w = place(a.carry);
   const int64_t n_units = (a.n + kUnit - 1) / kUnit;
   for (int64_t u = w.at; u < n_units; u += w.stride) {
-    const int64_t base = u * kUnit + w.lane * kVec;
-    const int64_t left = a.n - base;
-    const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
+    const int64_t base = u * kUnit + w.lane * 4;
+    const bool full = (u + 1) * kUnit <= a.n;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float prev[8], buf[8];
-    if (cnt == kVec) {
+    float prev[8] = {}, buf[8] = {};
+    if (full) {
       if constexpr (OUTER) {
-        load_f32x8(a.prev + base, prev);
-        load_f32x8(a.buf + base, buf);
+        load_f32x8<kHalves>(a.prev + base, prev);
+        load_f32x8<kHalves>(a.buf + base, buf);
       }
-      sum_streams<GT>([&](int k) { return a.reps[k] + base; }, a.G,
-                      [&](int k, u32x4 w) { fma_free_bf16x8(acc, a.w[k], w); });
+      sum_streams<GT, kHalves>([&](int k) { return a.reps[k] + base; }, a.G,
+                               [&](int k, u32x4 x) { fma_free_bf16x8(acc, a.w[k], x); });
     } else {
-      for (int e = 0; e < cnt; ++e) {
-        float s = 0.f;
-        for (int k = 0; k < a.G; ++k)
-          s = s + (a.w[k] * __uint_as_float((uint32_t)a.reps[k][base + e] << 16));
-        acc[e] = s;
-        if constexpr (OUTER) {
-          prev[e] = a.prev[base + e];
-          buf[e] = a.buf[base + e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = base + (e / 4) * kHalves + e % 4;
+        if (i < a.n) {
+          for (int k = 0; k < a.G; ++k)
+            acc[e] = acc[e] + (a.w[k] * __uint_as_float((uint32_t)a.reps[k][i] << 16));
+          if constexpr (OUTER) {
+            prev[e] = a.prev[i];
+            buf[e] = a.buf[i];
+          }
         }
       }
     }
     if constexpr (OUTER) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        if (e < cnt) {
-          const float delta = prev[e] - acc[e];
-          const float b = (a.mu * buf[e]) + delta;
-          const float d = a.nesterov ? (delta + (a.mu * b)) : b;
-          acc[e] = prev[e] - (a.eta * d);
-          buf[e] = b;
-        }
+        const float delta = prev[e] - acc[e];
+        const float b = (a.mu * buf[e]) + delta;
+        const float d = a.nesterov ? (delta + (a.mu * b)) : b;
+        acc[e] = prev[e] - (a.eta * d);
+        buf[e] = b;
       }
     }
     if constexpr (!OUTER) pause();
-    if (cnt == kVec) {
-      store_f32x8(a.master + base, acc);
-      st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(acc));
+    if (full) {
+      store_f32x8<kHalves>(a.master + base, acc);
+      store_bf16_halves(a.working + base, acc);
       if constexpr (OUTER) {
-        store_f32x8(a.prev + base, acc);
-        store_f32x8(a.buf + base, buf);
+        store_f32x8<kHalves>(a.prev + base, acc);
+        store_f32x8<kHalves>(a.buf + base, buf);
       }
     } else {
-      for (int e = 0; e < cnt; ++e) {
-        a.master[base + e] = acc[e];
-        a.working[base + e] = (uint16_t)to_bf16(acc[e]);
-        if constexpr (OUTER) {
-          a.prev[base + e] = acc[e];
-          a.buf[base + e] = buf[e];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = base + (e / 4) * kHalves + e % 4;
+        if (i < a.n) {
+          a.master[i] = acc[e];
+          a.working[i] = (uint16_t)to_bf16(acc[e]);
+          if constexpr (OUTER) {
+            a.prev[i] = acc[e];
+            a.buf[i] = buf[e];
+          }
         }
       }
     }
@@ -816,21 +848,22 @@ __global__ void __launch_bounds__(64) k_bcast_recv(const BcastArgs a) {
   const int64_t n = a.n;
   const int64_t n_units = (n + kUnit - 1) / kUnit;
   for (int64_t ui = at.at; ui < n_units; ui += at.stride) {
-    const int64_t base = ui * kUnit + at.lane * kVec;
-    const int64_t left = n - base;
-    if (left >= kVec) {
-      float x[8];
+    const int64_t base = ui * kUnit + at.lane * 4;
+    if ((ui + 1) * kUnit <= n) {
       const f32x4 u = ld_once(reinterpret_cast<const f32x4*>(a.recv + base));
-      const f32x4 w = ld_once(reinterpret_cast<const f32x4*>(a.recv + base + 4));
-      x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
-      x[4] = w.x; x[5] = w.y; x[6] = w.z; x[7] = w.w;
-      store_f32x8(a.master + base, x);
-      st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(x));
+      const f32x4 w = ld_once(reinterpret_cast<const f32x4*>(a.recv + base + kHalves));
+      loads_out();
+      const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
+      store_f32x8<kHalves>(a.master + base, x);
+      store_bf16_halves(a.working + base, x);
     } else {
-      for (int e = 0; e < (int)left; ++e) {
-        const float x = a.recv[base + e];
-        a.master[base + e] = x;
-        a.working[base + e] = (uint16_t)to_bf16(x);
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = base + (e / 4) * kHalves + e % 4;
+        if (i < n) {
+          const float x = a.recv[i];
+          a.master[i] = x;
+          a.working[i] = (uint16_t)to_bf16(x);
+        }
       }
     }
   }
