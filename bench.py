@@ -83,6 +83,7 @@ def round_kernels(w):
     n = w.n
     ks = []
     r = w.H if w.H > 1 else w.R
+    rt = 99 if r > 24 else _rt(r)   # the step's generic count on whole vectors
     if w.H > 1:
         wire = "k_reduce<%d, 3, false, %d>" % (_rt(w.R), 2 if w.R == 1 else 1)
         ks.append((wire, 2 * w.R * n, 2 * n))
@@ -91,9 +92,9 @@ def round_kernels(w):
         ks.append(("k_step<1, 2, 0>", 16 * n, 14 * n))
     elif w.max_grad_norm > 0:
         ks.append(("k_reduce<%d, 4, true, %d>" % (_rt(r), 4 if r <= 2 else 1), 2 * r * n, 0))
-        ks.append(("k_step<%d, 0, 0>" % _rt(r), (2 * r + 12) * n, 14 * n))
+        ks.append(("k_step<%d, 0, 0>" % rt, (2 * r + 12) * n, 14 * n))
     else:
-        ks.append(("k_step<%d, 0, %d>" % (_rt(r), 2 if 3 <= r <= 12 and n >= 384 << 17 else 1), (2 * r + 12) * n, 14 * n))
+        ks.append(("k_step<%d, 0, %d>" % (rt, 2 if 3 <= r <= 12 and n >= 384 << 17 else 1), (2 * r + 12) * n, 14 * n))
     if w.H > 1 and not w.hsdp_member:
         ks.append(("k_bcast_recv", 4 * n, 6 * n))
     elif w.outer is not None:

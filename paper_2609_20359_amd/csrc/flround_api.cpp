@@ -182,14 +182,15 @@ struct Pass {
   int units = 1;  // units a workgroup takes at a time
 };
 
-// step: R=1 5.84/5.49, R=2 5.93/5.45, R=4 5.95/5.41, R=6 5.99/5.47, R=8
-// 6.04/5.59, R=12 6.01/5.63, R=16 6.03/5.56, R=64 5.61/5.42.
+// step: R=1 5.98/5.35, R=2 6.02/5.38, R=4 5.98/5.36, R=6 6.05/5.35, R=8
+// 6.08/5.39, R=12 6.05/5.67, R=16 6.09/5.66, R=64 5.61/5.42 (16 waves for the
+// second figure).
 Pass step_pass(int R) {
-  const int w = R <= 2 ? 8 : R <= 4 ? 6 : R <= 12 ? 5 : 4;
+  const int w = R <= 2 ? 7 : R <= 4 ? 6 : R <= 12 ? 5 : 4;
   return {w, w + 2, 2 * w};
 }
-// AdamW alone: 5.83/5.35.
-constexpr Pass kAdamPass = {6, 8, 9};
+// AdamW alone: 5.95/5.19.
+constexpr Pass kAdamPass = {5, 7, 9};
 // Sums of squares only: R=1 3.99 with four units per workgroup and 3.36 with
 // one, R=2 6.05 and 5.70, R=4 6.47/6.35, R=8 6.70/6.47, R=16 6.68/6.66, R=32
 // 6.75/6.67.
@@ -198,10 +199,9 @@ Pass sumsq_pass(int R) {
   const int w = R <= 3 ? 24 : R <= 5 ? 20 : R <= 7 ? 14 : R <= 12 ? 10 : 7;
   return {w, w, 2 * w};
 }
-// To fp32: R=1 5.08/5.19, R=2 5.53/5.58, R=4 6.11/5.91, R=8 6.45/6.10, R=16
-// 6.33/5.89, R=32 5.95/5.75.
+// To fp32: R=1 6.06, R=4 6.53/6.47, R=8 6.63/6.00, R=32 6.09/5.62.
 Pass reduce_pass(int R) {
-  const int w = R <= 3 ? 24 : R <= 6 ? 12 : R <= 12 ? 8 : 6;
+  const int w = R <= 3 ? 24 : R <= 6 ? 14 : R <= 12 ? 7 : 6;
   return {w, w, 2 * w};
 }
 // To the wire format: R=1 6.75 with two units per workgroup and 6.44 with

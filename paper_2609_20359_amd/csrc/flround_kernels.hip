@@ -153,9 +153,9 @@ __device__ __forceinline__ void fma_free_bf16x8(float acc[8], float wt, u32x4 w)
 // Where a lane's 8 elements lie.  kWhole: 8 in a row, one 16-byte access per
 // bf16 stream and two of fp32, each of which covers every other 16 bytes of the
 // wave's lines.  kHalves: elements 4l .. 4l + 3 of each half of the unit, so
-// that one fp32 access covers whole lines.  Passes that read little for what
-// they write run on halves: whole, their lines left the L2 half written
-// (broadcast receive 1.12 of its bytes written, FedAvg G=4 1.03).
+// that one fp32 access covers whole lines.  Passes that write fp32 run on
+// halves: whole, some of their lines left the L2 half written (broadcast receive
+// 1.12 of its bytes written, the reduction to fp32 1.10, FedAvg G=4 1.03).
 constexpr int kWhole = 4, kHalves = kUnit / 2;  // distance of the second four
 
 template <int kGap = kWhole>
@@ -183,11 +183,15 @@ __device__ __forceinline__ u32x4 load_bf16x8(const uint16_t* p) {
   }
 }
 
-// (on halves)
-__device__ __forceinline__ void store_bf16_halves(uint16_t* p, const float x[8]) {
+template <int kGap>
+__device__ __forceinline__ void store_bf16x8(uint16_t* p, const float x[8]) {
   const u32x4 w = pack_bf16x8(x);
-  st(reinterpret_cast<u32x2*>(p), u32x2{w.x, w.y});
-  st(reinterpret_cast<u32x2*>(p + kHalves), u32x2{w.z, w.w});
+  if constexpr (kGap == kWhole) {
+    st(reinterpret_cast<u32x4*>(p), w);
+  } else {
+    st(reinterpret_cast<u32x2*>(p), u32x2{w.x, w.y});
+    st(reinterpret_cast<u32x2*>(p + kGap), u32x2{w.z, w.w});
+  }
 }
 
 // Sum over n bf16 streams of element e of a full vector, streams in ascending
@@ -244,25 +248,27 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
 __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(4); }
 
 // Reduced gradient of 8 elements (full vector): peers in ascending order.
-template <int RT>
+template <int RT, int kGap = kWhole>
 __device__ __forceinline__ void reduce_vec(const StepArgs& a, int64_t base, float g[8]) {
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  sum_streams<RT>([&](int r) { return a.grads[r] + base; }, a.R,
+  sum_streams<RT, kGap>([&](int r) { return a.grads[r] + base; }, a.R,
                   [&](int, u32x4 w) { add_bf16x8(acc, w); });
 #pragma unroll
   for (int e = 0; e < 8; ++e) g[e] = acc[e] * a.grad_scale;
 }
 
-// Same for the last, partial vector: elements base .. base + cnt - 1.
-__device__ __forceinline__ void reduce_tail(const StepArgs& a, int64_t base, int cnt,
-                                            float g[8]) {
+// Same for a unit that the shard's end cuts: one element at a time, 0 past it.
+template <int kGap>
+__device__ __forceinline__ void reduce_some(const StepArgs& a, int64_t base, float g[8]) {
+#pragma unroll
   for (int e = 0; e < 8; ++e) {
+    const int64_t i = base + (e / 4) * kGap + e % 4;
     float acc = 0.f;
-    if (e < cnt) {
+    if (i < a.L.n) {
       for (int r = 0; r < a.R; ++r)
-        acc = acc + __uint_as_float((uint32_t)a.grads[r][base + e] << 16);
+        acc = acc + __uint_as_float((uint32_t)a.grads[r][i] << 16);
     }
-    g[e] = acc * a.grad_scale;
+    g[e] = i < a.L.n ? acc * a.grad_scale : 0.f;
   }
 }
 
@@ -444,15 +450,22 @@ __device__ __forceinline__ UnitSegs unit_segs(const LayoutDev& L, const TileInfo
   return s;
 }
 
-// Segment of each element of a lane's vector, for a unit of several.
+// Segment of each of a lane's elements, for a unit of several; -1 past the
+// shard's end.
+template <int kGap>
 __device__ __forceinline__ void lane_segs(const LayoutDev& L, const UnitSegs& us, int64_t base,
-                                          int cnt, int seg[8]) {
-  int s = cnt > 0 ? find_seg(L.seg_off, us.lo, us.hi, base) : us.lo;
+                                          int seg[8]) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (e < cnt)
-      while (base + e >= L.seg_off[s + 1]) ++s;
-    seg[e] = s;
+  for (int h = 0; h < 2; ++h) {
+    const int64_t b = base + h * kGap;
+    int s = b < L.n ? find_seg(L.seg_off, us.lo, us.hi, b) : -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (b + e >= L.n) s = -1;
+      if (s >= 0)
+        while (b + e >= L.seg_off[s + 1]) ++s;
+      seg[h * 4 + e] = s;
+    }
   }
 }
 
@@ -463,16 +476,17 @@ __device__ __forceinline__ double add_square(double acc, float x) {
 
 // Sums of squares of unit u: one partial per (piece, unit) of its tile, the
 // exact double squares of a lane's 8 elements summed in order, then the wave
-// butterfly; 0 for the tile's segments that the unit does not touch.
+// butterfly; 0 for the tile's segments that the unit does not touch.  (g is 0
+// past the shard's end.)
 template <bool LDS = false>
 __device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us, int64_t u,
-                                           int lane, int cnt, const int seg[8],
+                                           int lane, const int seg[8],
                                            const float g[8]) {
   double* out = partials + (int64_t)us.ti.piece0 * kWaves + u % kWaves;
   if (us.lo == us.hi) {
     double acc = 0.0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) if (e < cnt) acc = add_square(acc, g[e]);
+    for (int e = 0; e < 8; ++e) acc = add_square(acc, g[e]);
     const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
     if (lane == 0) out[(int64_t)(us.lo - us.ti.seg0) * kWaves] = tot;
   } else {
@@ -480,7 +494,7 @@ __device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us,
       double acc = 0.0;
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (e < cnt && seg[e] == sj) acc = add_square(acc, g[e]);
+        if (seg[e] == sj) acc = add_square(acc, g[e]);
       const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
       if (lane == 0) out[(int64_t)(sj - us.ti.seg0) * kWaves] = tot;
     }
@@ -565,17 +579,24 @@ __device__ __forceinline__ void adam8(const AdamScalars& s, const float g[8], fl
 // gradient g_in.  The gradient is scaled by the clip coefficient when
 // a.clip_total is set.  SUMS 1: per-piece sums of squares of g (before
 // clipping); 2: the same, exchanged by way of LDS.
+// Elements on halves: the 8B shard's step (R = 8) runs at 6.38 TB/s and 6.24 on
+// whole vectors, the 1 Mi round takes 31.7 and 34.0 us.  RT kMany (the generic
+// count, for more than 24 peers): on whole vectors, as twice the loads cost more
+// than whole lines give (R = 64 5.56 TB/s on halves, 5.62 whole).
+constexpr int kMany = 99;
+
 template <int RT, int MODE, int SUMS>
 __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
-  args_in<MODE == 2 ? 1 : RT == 0 ? 8 : RT>(a);
+  constexpr int kGap = RT == kMany ? kWhole : kHalves;
+  constexpr int kStreams = RT == kMany ? 0 : RT;
+  args_in<MODE == 2 ? 1 : kStreams == 0 ? 8 : kStreams>(a);
   if (run_carry(a.carry)) return;
   const Place w = place(a.carry);
   const int lane = w.lane;
   const int64_t n_units = a.L.n_tiles * kWaves;  // past n too: their partials are 0
   for (int64_t u = w.at; u < n_units; u += w.stride) {
-    const int64_t base = u * kUnit + lane * kVec;
-    const int64_t left = a.L.n - base;
-    const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
+    const int64_t base = u * kUnit + lane * (kGap == kWhole ? kVec : 4);
+    const bool full = (u + 1) * kUnit <= a.L.n;
 
     // asked for before the streams, so that it is there when they are
     i32x4 tile = ld_uniform(reinterpret_cast<const i32x4*>(a.L.tiles) + u / kWaves);
@@ -585,28 +606,29 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
 
     float g[8];
     float p[8], m[8], v[8];
-    if (cnt == kVec) {
-      load_f32x8(a.master + base, p);
-      load_f32x8(a.m + base, m);
-      load_f32x8(a.v + base, v);
+    if (full) {
+      load_f32x8<kGap>(a.master + base, p);
+      load_f32x8<kGap>(a.m + base, m);
+      load_f32x8<kGap>(a.v + base, v);
       if constexpr (MODE == 2) {
-        load_f32x8(a.g_in + base, g);
+        load_f32x8<kGap>(a.g_in + base, g);
         loads_out();
       } else {
-        reduce_vec<RT>(a, base, g);
+        reduce_vec<kStreams, kGap>(a, base, g);
       }
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
+        const int64_t i = base + (e / 4) * kGap + e % 4;
         p[e] = 0.f; m[e] = 0.f; v[e] = 0.f; g[e] = 0.f;
-        if (e < cnt) { p[e] = a.master[base + e]; m[e] = a.m[base + e]; v[e] = a.v[base + e]; }
-        if constexpr (MODE == 2) {
-          if (e < cnt) g[e] = a.g_in[base + e];
+        if (i < a.L.n) {
+          p[e] = a.master[i];
+          m[e] = a.m[i];
+          v[e] = a.v[i];
+          if constexpr (MODE == 2) g[e] = a.g_in[i];
         }
       }
-      if constexpr (MODE != 2) {
-        if (cnt > 0) reduce_tail(a, base, cnt, g);
-      }
+      if constexpr (MODE != 2) reduce_some<kGap>(a, base, g);
     }
 
     // (not looked at before the streams' loads are out)
@@ -614,7 +636,7 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
     const TileInfo ti{tile.x, tile.y, tile.z, tile.w};
     const UnitSegs us = unit_segs(a.L, ti, u);
     int seg[8];
-    if (us.lo != us.hi) lane_segs(a.L, us, base, cnt, seg);
+    if (us.lo != us.hi) lane_segs<kGap>(a.L, us, base, seg);
 
     const AdamScalars& s = a.s;
     const float coef = clip ? clip_coef(total, a.clip_max) : 1.0f;
@@ -629,25 +651,29 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
       for (int e = 0; e < 8; ++e) d[e] = du;
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) d[e] = e < cnt && a.L.seg_decay[seg[e]] ? s.decay : 1.0f;
+      for (int e = 0; e < 8; ++e) d[e] = seg[e] >= 0 && a.L.seg_decay[seg[e]] ? s.decay : 1.0f;
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = p[e] * d[e];
     adam8(s, gc, p, m, v);
-    if (cnt == kVec) {
-      store_f32x8(a.master + base, p);
-      store_f32x8(a.m + base, m);
-      store_f32x8(a.v + base, v);
-      if (MODE == 0 || a.working) st(reinterpret_cast<u32x4*>(a.working + base), pack_bf16x8(p));
+    if (full) {
+      store_f32x8<kGap>(a.master + base, p);
+      store_f32x8<kGap>(a.m + base, m);
+      store_f32x8<kGap>(a.v + base, v);
+      if (MODE == 0 || a.working) store_bf16x8<kGap>(a.working + base, p);
     } else {
-      for (int e = 0; e < cnt; ++e) {
-        a.master[base + e] = p[e];
-        a.m[base + e] = m[e];
-        a.v[base + e] = v[e];
-        if (MODE == 0 || a.working) a.working[base + e] = (uint16_t)to_bf16(p[e]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t i = base + (e / 4) * kGap + e % 4;
+        if (i < a.L.n) {
+          a.master[i] = p[e];
+          a.m[i] = m[e];
+          a.v[i] = v[e];
+          if (MODE == 0 || a.working) a.working[i] = (uint16_t)to_bf16(p[e]);
+        }
       }
     }
-    if constexpr (SUMS != 0) unit_sumsq<SUMS == 2>(a.partials, us, u, lane, cnt, seg, g);
+    if constexpr (SUMS != 0) unit_sumsq<SUMS == 2>(a.partials, us, u, lane, seg, g);
   }
 }
 
@@ -661,6 +687,9 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
   if (run_carry(a.carry)) return;
   const Place w = place(a.carry);
   const int lane = w.lane;
+  // an fp32 output is written on halves
+  constexpr int kGap = OUT == 1 ? kHalves : kWhole;
+  const int at = lane * (OUT == 1 ? 4 : kVec);
   const int64_t n_groups = a.L.n_tiles * (kWaves / NV);
   for (int64_t b = w.at; b < n_groups; b += w.stride) {
     const int64_t u0 = b * NV;
@@ -669,7 +698,7 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
     float g[NV][8];
     if ((u0 + NV) * kUnit <= a.L.n) {
       if constexpr (NV == 1) {
-        reduce_vec<RT>(a, u0 * kUnit + lane * kVec, g[0]);
+        reduce_vec<RT, kGap>(a, u0 * kUnit + at, g[0]);
       } else {
         u32x4 x[NV][RT];
 #pragma unroll
@@ -690,30 +719,29 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int64_t base = (u0 + i) * kUnit + lane * kVec;
-        const int64_t left = a.L.n - base;
-        if (left >= kVec) reduce_vec<RT>(a, base, g[i]);
-        else reduce_tail(a, base, left > 0 ? (int)left : 0, g[i]);
-      }
+      for (int i = 0; i < NV; ++i)
+        reduce_some<kGap>(a, (u0 + i) * kUnit + at, g[i]);
     }
     if constexpr (OUT == 3) pause();
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int64_t base = (u0 + i) * kUnit + lane * kVec;
-      const int64_t left = a.L.n - base;
-      const int cnt = left >= kVec ? kVec : (left > 0 ? (int)left : 0);
+      const int64_t base = (u0 + i) * kUnit + at;
+      const bool full = (u0 + i + 1) * kUnit <= a.L.n;
       if constexpr (OUT == 1) {
-        if (cnt == kVec) {
-          store_f32x8(a.g_out + base, g[i]);
-        } else {
-          for (int e = 0; e < cnt; ++e) a.g_out[base + e] = g[i][e];
-        }
+        if (full) store_f32x8<kGap>(a.g_out + base, g[i]);
       } else if constexpr (OUT == 3) {
-        if (cnt == kVec) {
-          st(reinterpret_cast<u32x4*>(a.wire_out + base), pack_bf16x8(g[i]));
-        } else {
-          for (int e = 0; e < cnt; ++e) a.wire_out[base + e] = (uint16_t)to_bf16(g[i][e]);
+        if (full) st(reinterpret_cast<u32x4*>(a.wire_out + base), pack_bf16x8(g[i]));
+      }
+      if constexpr (OUT != 4) {
+        if (!full) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int64_t k = base + (e / 4) * kGap + e % 4;
+            if (k < a.L.n) {
+              if constexpr (OUT == 1) a.g_out[k] = g[i][e];
+              else a.wire_out[k] = (uint16_t)to_bf16(g[i][e]);
+            }
+          }
         }
       }
       if constexpr (SUMSQ) {
@@ -721,8 +749,8 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
         const TileInfo ti{tile.x, tile.y, tile.z, tile.w};
         const UnitSegs us = unit_segs(a.L, ti, u0 + i);
         int seg[8];
-        if (us.lo != us.hi) lane_segs(a.L, us, base, cnt, seg);
-        unit_sumsq(a.partials, us, u0 + i, lane, cnt, seg, g[i]);
+        if (us.lo != us.hi) lane_segs<kGap>(a.L, us, base, seg);
+        unit_sumsq(a.partials, us, u0 + i, lane, seg, g[i]);
       }
     }
   }
@@ -777,7 +805,7 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
     if constexpr (!OUTER) pause();
     if (full) {
       store_f32x8<kHalves>(a.master + base, acc);
-      store_bf16_halves(a.working + base, acc);
+      store_bf16x8<kHalves>(a.working + base, acc);
       if constexpr (OUTER) {
         store_f32x8<kHalves>(a.prev + base, acc);
         store_f32x8<kHalves>(a.buf + base, buf);
@@ -855,7 +883,7 @@ __global__ void __launch_bounds__(64) k_bcast_recv(const BcastArgs a) {
       loads_out();
       const float x[8] = {u.x, u.y, u.z, u.w, w.x, w.y, w.z, w.w};
       store_f32x8<kHalves>(a.master + base, x);
-      store_bf16_halves(a.working + base, x);
+      store_bf16x8<kHalves>(a.working + base, x);
     } else {
       for (int e = 0; e < 8; ++e) {
         const int64_t i = base + (e / 4) * kHalves + e % 4;
@@ -888,7 +916,9 @@ hipError_t dispatch_step(const StepArgs& a, Shape sh, hipStream_t st) {
     case 6: return launch((const void*)k_step<6, 0, SUMS>, a, sh, st);
     case 7: return launch((const void*)k_step<7, 0, SUMS>, a, sh, st);
     case 8: return launch((const void*)k_step<8, 0, SUMS>, a, sh, st);
-    default: return launch((const void*)k_step<0, 0, SUMS>, a, sh, st);
+    default:
+      return launch(a.R > 24 ? (const void*)k_step<kMany, 0, SUMS>
+                             : (const void*)k_step<0, 0, SUMS>, a, sh, st);
   }
 }
 
