@@ -168,7 +168,7 @@ int check_device(const fl_layout* lay) {
 // index order, which keeps the units in flight a narrow window of each array.
 // (Resident workgroups striding over the shard drift apart: with one such
 // workgroup of four waves per CU the 8B shard's step, R = 8, took 7.60 ms,
-// with two 8.6 ms, with this 6.65 ms.)  And a CU holds only as many waves as
+// with two 8.6 ms, in order 6.88 ms.)  And a CU holds only as many waves as
 // cover the latency: more widen the window, fewer leave gaps.  The limit is
 // set by LDS that a workgroup asks for and does not use.
 //
@@ -255,8 +255,9 @@ flr::Shape shape_for(const fl_layout* lay, Pass pass) {
 
 // Whether a fused step's per-segment sums exchange their partials by way of
 // LDS, later than by DPP moves and with the same bits.  Long passes of a few
-// streams run faster so (R=8 on 1.0e9 elements 6.24 TB/s and 6.15, R=4 6.13 and
-// 6.03, R=4 on 5.0e8 5.96 and 5.81), the others slower (R=16 on 5.0e8 5.89 and
+// streams run faster so (measured on whole vectors: R=8 on
+// 1.0e9 elements 6.24 TB/s and 6.15, R=4 6.13 and 6.03, R=4 on 5.0e8 5.96 and
+// 5.81), the others slower (R=16 on 5.0e8 5.89 and
 // 6.02, R=2 on 6.3e7 5.47 and 5.57, the 1 Mi round 4.24 and 4.36).
 int step_sum_by_lds(const fl_layout* lay, int R) {
   return R >= 3 && R <= 12 && lay->L.n_tiles * flr::kWaves / lay->num_cus >= kMid;

@@ -3,11 +3,11 @@
 // Every kernel here is a bandwidth-bound stream over the flat shard: an
 // element is read once, updated with a few dozen fp32 operations and written
 // once, so the kernels are built for HBM, not for the matrix cores:
-//   * a workgroup is one wave64 and takes one unit of 512 elements; each lane
-//     owns 8 consecutive elements, i.e. one 16-byte load per bf16 stream and
-//     two per fp32 stream (global_load_dwordx4), so a wave touches whole
-//     128-byte lines.  The grid has a workgroup for every unit, and how many
-//     a CU holds at once is limited per pass (the launch shapes say why);
+//   * a workgroup is one wave64 and takes one unit of 512 elements, 8 to a
+//     lane: 4 of each half of the unit in the passes that write fp32, 8 in a
+//     row in the others (kHalves and kWhole say why).  The grid has a workgroup
+//     for every unit, and how many a CU holds at once is limited per pass (the
+//     launch shapes say why);
 //   * all loads of a unit are out before its arithmetic, the layout table's by
 //     way of the scalar cache: a wave waits for memory once;
 //   * sums over peers and replicas run in ascending index order in fp32, one
@@ -241,8 +241,8 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
 // A pause of 256 clocks between a wave's last addition and its stores.  Passes
 // that do little else run faster with it: to the wire format R=4 6.90 TB/s and
 // 6.43 without (12 waves per CU, 5e8 elements; 6.65 without at its best, 14),
-// R=8 on 6.3e7 elements 6.91 and 6.76, FedAvg G=4 6.41 and 6.32, G=5 on 5e7
-// 6.27 and 6.17; twice the pause gives no more, half of it half.  It was found
+// R=8 on 6.3e7 elements 6.91 and 6.76, FedAvg G=4 (on whole vectors) 6.41 and
+// 6.32, G=5 on 5e7 6.27 and 6.17; twice the pause gives no more, half of it half.  It was found
 // when the bf16 rounding, in its place before, became one instruction.  With
 // AdamW between loads and stores it makes no difference.
 __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(4); }
