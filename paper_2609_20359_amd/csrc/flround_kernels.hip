@@ -273,32 +273,54 @@ __device__ __forceinline__ void reduce_some(const StepArgs& a, int64_t base, flo
 }
 
 // Fixed-tree sum over one wave64, all lanes active: the butterfly of
-// exchanges with lanes 1, 2, 4, 8, 16 and 32 away, the same in every lane.
-// The first four are DPP moves (after two the lanes of a quad agree, after
-// three those of a half row, so a mirror reaches what the exchange would),
-// the last two read one lane of each row.  wave_sum_lds is the same tree by
-// way of LDS, twelve dependent trips: the same bits, later.
+// exchanges with lanes 32, 16, 8, 4, 2 and 1 away, in this order, the same in
+// every lane.  The first two swap halves and rows between two copies of the
+// value, so that a lane's two copies are its own and its partner's; the others
+// are DPP moves (once the lanes 8 apart agree, a rotation by 4 within a row
+// reaches what the exchange would).  wave_sum_lds is the same tree by way of
+// LDS, twelve dependent trips: the same bits, later.
+__device__ __forceinline__ double of_words(uint32_t lo, uint32_t hi) {
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 template <int kCtrl>
-__device__ __forceinline__ double dpp(double v) {
+__device__ __forceinline__ double add_dpp(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)u, kCtrl, 0xF, 0xF, true);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), kCtrl, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  return v + of_words(lo, hi);
 }
 
-__device__ __forceinline__ double lane_of(double v, int lane) {
+template <int kOff>
+__device__ __forceinline__ double add_lane_xor(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)u, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(u >> 32), lane);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  const uint32_t l = (uint32_t)u, h = (uint32_t)(u >> 32);
+  if constexpr (kOff == 32) {
+    const u32x2 lo = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const u32x2 hi = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return of_words(lo.x, hi.x) + of_words(lo.y, hi.y);
+  } else if constexpr (kOff == 16) {
+    const u32x2 lo = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+    const u32x2 hi = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+    return of_words(lo.x, hi.x) + of_words(lo.y, hi.y);
+  } else if constexpr (kOff == 8) {
+    return add_dpp<0x128>(v);  // row_ror:8
+  } else if constexpr (kOff == 4) {
+    return add_dpp<0x124>(v);  // row_ror:4
+  } else if constexpr (kOff == 2) {
+    return add_dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+  } else {
+    return add_dpp<0xB1>(v);   // quad_perm [1,0,3,2]
+  }
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
-  v = v + dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-  v = v + dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-  v = v + dpp<0x141>(v);  // row_half_mirror
-  v = v + dpp<0x140>(v);  // row_mirror
-  return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+  v = add_lane_xor<32>(v);
+  v = add_lane_xor<16>(v);
+  v = add_lane_xor<8>(v);
+  v = add_lane_xor<4>(v);
+  v = add_lane_xor<2>(v);
+  return add_lane_xor<1>(v);
 }
 
 __device__ __forceinline__ double wave_sum_lds(double v) {
