@@ -284,11 +284,11 @@ __device__ __forceinline__ double of_words(uint32_t lo, uint32_t hi) {
 }
 
 template <int kCtrl>
-__device__ __forceinline__ double add_dpp(double v) {
+__device__ __forceinline__ double from_dpp(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)u, kCtrl, 0xF, 0xF, true);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(u >> 32), kCtrl, 0xF, 0xF, true);
-  return v + of_words(lo, hi);
+  return of_words(lo, hi);
 }
 
 template <int kOff>
@@ -304,28 +304,41 @@ __device__ __forceinline__ double add_lane_xor(double v) {
     const u32x2 hi = __builtin_amdgcn_permlane16_swap(h, h, false, false);
     return of_words(lo.x, hi.x) + of_words(lo.y, hi.y);
   } else if constexpr (kOff == 8) {
-    return add_dpp<0x128>(v);  // row_ror:8
+    return v + from_dpp<0x128>(v);  // row_ror:8
   } else if constexpr (kOff == 4) {
-    return add_dpp<0x124>(v);  // row_ror:4
+    return v + from_dpp<0x124>(v);  // row_ror:4
   } else if constexpr (kOff == 2) {
-    return add_dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+    return v + from_dpp<0x4E>(v);   // quad_perm [2,3,0,1]
   } else {
-    return add_dpp<0xB1>(v);   // quad_perm [1,0,3,2]
+    return v + from_dpp<0xB1>(v);   // quad_perm [1,0,3,2]
   }
 }
 
+//
+// kLast: the last exchange, 1 or 2.  With 2 the odd lanes hold the sums of the
+// tree's lanes l and l + 32 (see unit_sum), and only they come out right.
+template <int kLast = 1>
 __device__ __forceinline__ double wave_sum(double v) {
-  v = add_lane_xor<32>(v);
-  v = add_lane_xor<16>(v);
-  v = add_lane_xor<8>(v);
-  v = add_lane_xor<4>(v);
-  v = add_lane_xor<2>(v);
-  return add_lane_xor<1>(v);
+  if constexpr (kLast == 1) {
+    v = add_lane_xor<32>(v);
+    v = add_lane_xor<16>(v);
+    v = add_lane_xor<8>(v);
+    v = add_lane_xor<4>(v);
+    v = add_lane_xor<2>(v);
+    return add_lane_xor<1>(v);
+  } else {
+    v = add_lane_xor<32>(v);
+    v = add_lane_xor<16>(v);
+    v = add_lane_xor<8>(v);
+    v = add_lane_xor<4>(v);
+    return add_lane_xor<2>(v);
+  }
 }
 
+template <int kLast = 1>
 __device__ __forceinline__ double wave_sum_lds(double v) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = v + __shfl_xor(v, off, 64);
+  for (int off = 32; off >= kLast; off >>= 1) v = v + __shfl_xor(v, off, 64);
   return v;
 }
 
@@ -496,29 +509,61 @@ __device__ __forceinline__ double add_square(double acc, float x) {
   return __builtin_fma((double)x, (double)x, acc);
 }
 
-// Sums of squares of unit u: one partial per (piece, unit) of its tile, the
-// exact double squares of a lane's 8 elements summed in order, then the wave
-// butterfly; 0 for the tile's segments that the unit does not touch.  (g is 0
-// past the shard's end.)
-template <bool LDS = false>
+// One partial, valid in lane kSumLane: the exact double squares of 8
+// consecutive elements summed in order, then the butterfly over the 64 groups
+// of 8.  On halves a lane has 4 of a group of each half, its first 4 if the lane
+// is even: the odd lanes go on from their neighbour's sums with their own 4 and
+// add the two halves' groups, lanes 32 apart in the tree.  So the tree over
+// element indices is the same in every pass, and the clip total has the same
+// bits with and without a gradient scratch.  Four steps of the 8B shard take
+// 28.41 ms with it and 28.41 when each lane summed what it holds, the 1 Mi round
+// 31.6 and 31.4 us; moving the elements between the lanes instead, 28.58 ms.
+template <int kGap>
+constexpr int kSumLane = kGap == kWhole ? 0 : 1;
+
+template <int kGap, bool LDS>
+__device__ __forceinline__ double unit_sum(const float g[8]) {
+  if constexpr (kGap == kWhole) {
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = add_square(acc, g[e]);
+    return LDS ? wave_sum_lds(acc) : wave_sum(acc);
+  } else {
+    double h0 = 0.0, h1 = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h0 = add_square(h0, g[e]);
+      h1 = add_square(h1, g[4 + e]);
+    }
+    h0 = from_dpp<0xB1>(h0);
+    h1 = from_dpp<0xB1>(h1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h0 = add_square(h0, g[e]);
+      h1 = add_square(h1, g[4 + e]);
+    }
+    return LDS ? wave_sum_lds<2>(h0 + h1) : wave_sum<2>(h0 + h1);
+  }
+}
+
+// Sums of squares of unit u: one partial per (piece, unit) of its tile; 0 for
+// the tile's segments that the unit does not touch.  (g is 0 past the shard's
+// end, and so are here the other segments' elements: adding 0 changes no bit.)
+template <int kGap, bool LDS = false>
 __device__ __forceinline__ void unit_sumsq(double* partials, const UnitSegs& us, int64_t u,
                                            int lane, const int seg[8],
                                            const float g[8]) {
   double* out = partials + (int64_t)us.ti.piece0 * kWaves + u % kWaves;
   if (us.lo == us.hi) {
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc = add_square(acc, g[e]);
-    const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
-    if (lane == 0) out[(int64_t)(us.lo - us.ti.seg0) * kWaves] = tot;
+    const double tot = unit_sum<kGap, LDS>(g);
+    if (lane == kSumLane<kGap>) out[(int64_t)(us.lo - us.ti.seg0) * kWaves] = tot;
   } else {
     for (int sj = us.lo; sj <= us.hi; ++sj) {
-      double acc = 0.0;
+      float of[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (seg[e] == sj) acc = add_square(acc, g[e]);
-      const double tot = LDS ? wave_sum_lds(acc) : wave_sum(acc);
-      if (lane == 0) out[(int64_t)(sj - us.ti.seg0) * kWaves] = tot;
+      for (int e = 0; e < 8; ++e) of[e] = seg[e] == sj ? g[e] : 0.f;
+      const double tot = unit_sum<kGap, LDS>(of);
+      if (lane == kSumLane<kGap>) out[(int64_t)(sj - us.ti.seg0) * kWaves] = tot;
     }
   }
   for (int j = lane; j < us.ti.nseg; j += 64)
@@ -695,7 +740,7 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
         }
       }
     }
-    if constexpr (SUMS != 0) unit_sumsq<SUMS == 2>(a.partials, us, u, lane, seg, g);
+    if constexpr (SUMS != 0) unit_sumsq<kGap, SUMS == 2>(a.partials, us, u, lane, seg, g);
   }
 }
 
@@ -772,7 +817,7 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
         const UnitSegs us = unit_segs(a.L, ti, u0 + i);
         int seg[8];
         if (us.lo != us.hi) lane_segs<kGap>(a.L, us, base, seg);
-        unit_sumsq(a.partials, us, u0 + i, lane, seg, g[i]);
+        unit_sumsq<kGap>(a.partials, us, u0 + i, lane, seg, g[i]);
       }
     }
   }

@@ -169,11 +169,45 @@ def test_long_and_short_steps_agree(env, R):
     print("step R=%d short" % R, flush=True)
     P.fl_local_step(short, ADAMW, 9, peers_of(torch, on_device(torch, g), R), 1.0,
                     *state(torch, n0), seg_sumsq=ss)
-    lay, t, _ = long_layout(torch, P, off, g)
+    lay, t, want = long_layout(torch, P, off, g)
     long_ss = torch.zeros(2 * (off.size - 1) + 1, device="cuda")
     print("step R=%d long n=%d" % (R, t.numel()), flush=True)
     P.fl_local_step(lay, ADAMW, 9, peers_of(torch, t, R), 1.0, *state(torch, t.numel()),
                     seg_sumsq=long_ss)
     assert torch.equal(long_ss[:off.size - 1], ss)
+    assert np.array_equal(ss.cpu().numpy(), np.float32(expected(off, g)[0]))
+    assert np.array_equal(long_ss.cpu().numpy(), np.float32(want))
     short.close()
+    lay.close()
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 8, 9, 26])
+def test_every_pass_adds_in_one_order(env, R):
+    """The reduction to fp32, the sums alone and the fused step, whose lanes
+    hold different elements, and a clipped round with and without the gradient
+    scratch: the same segments' floats, and the same state."""
+    torch, P = env
+    off, g = shaped(lengths(20 + R), 20 + R)
+    n = int(off[-1])
+    want = np.float32(expected(off, g)[0])
+    lay = P.Layout(off, np.ones(off.size - 1, np.uint8))
+    peers = peers_of(torch, on_device(torch, g), R)
+    ss = torch.zeros(off.size - 1, device="cuda")
+    print("passes R=%d n=%d" % (R, n), flush=True)
+    P.fl_shard_reduce(lay, peers, 1.0, torch.empty(n, device="cuda"), seg_sumsq=ss)
+    assert np.array_equal(ss.cpu().numpy(), want)
+    P.fl_grad_sumsq(lay, peers, 1.0, torch.zeros(1, dtype=torch.float64, device="cuda"),
+                    seg_sumsq=ss.zero_())
+    assert np.array_equal(ss.cpu().numpy(), want)
+    P.fl_local_step(lay, ADAMW, 9, peers, 1.0, *state(torch, n), seg_sumsq=ss.zero_())
+    assert np.array_equal(ss.cpu().numpy(), want)
+    out = []
+    for scratch in (None, torch.empty(n, device="cuda")):
+        cfg = P.make_round_cfg(R, 1, 1, [1.0], ADAMW, step0=9, grad_scale=1.0, max_grad_norm=1.0,
+                               grad_scratch=scratch)
+        st = state(torch, n)
+        P.fl_round(lay, cfg, peers, [None], *st, seg_sumsq=ss.zero_())
+        assert np.array_equal(ss.cpu().numpy(), want)
+        out.append(st)
+    assert all(torch.equal(a, b) for a, b in zip(*out))
     lay.close()
