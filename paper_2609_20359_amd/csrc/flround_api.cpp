@@ -170,7 +170,8 @@ int check_device(const fl_layout* lay) {
 // workgroup of four waves per CU the 8B shard's step, R = 8, took 7.60 ms,
 // with two 8.6 ms, in order 6.88 ms.)  And a CU holds only as many waves as
 // cover the latency: more widen the window, fewer leave gaps.  The limit is
-// set by LDS that a workgroup asks for and does not use.
+// set by LDS that a workgroup asks for and does not use, in steps of a CU's
+// 128th: 6 of them are 21 waves, 5 are 25, and from 26 on there is no limit.
 //
 // The limits are the best of sweeps of 3 to 32 waves per CU on 5e8 elements;
 // the figures are TB/s at the limit taken, and at 32.  The fewer bytes a wave
@@ -195,20 +196,20 @@ constexpr Pass kAdamPass = {5, 7, 9};
 // one, R=2 6.05 and 5.70, R=4 6.47/6.35, R=8 6.70/6.47, R=16 6.68/6.66, R=32
 // 6.75/6.67.
 Pass sumsq_pass(int R) {
-  if (R <= 2) return {24, 24, 24, 4};
-  const int w = R <= 3 ? 24 : R <= 5 ? 20 : R <= 7 ? 14 : R <= 12 ? 10 : 7;
+  if (R <= 2) return {25, 25, 25, 4};
+  const int w = R <= 3 ? 25 : R <= 5 ? 21 : R <= 7 ? 14 : R <= 12 ? 10 : 7;
   return {w, w, 2 * w};
 }
 // To fp32: R=1 6.06, R=4 6.53/6.47, R=8 6.63/6.00, R=32 6.09/5.62.
 Pass reduce_pass(int R) {
-  const int w = R <= 3 ? 24 : R <= 6 ? 14 : R <= 12 ? 7 : 6;
+  const int w = R <= 3 ? 25 : R <= 6 ? 14 : R <= 12 ? 7 : 6;
   return {w, w, 2 * w};
 }
 // To the wire format: R=1 6.75 with two units per workgroup and 6.44 with
 // one, R=2 6.78/6.78, R=4 6.94/6.38, R=8 6.68/6.21, R=16 6.52/6.21, R=32
 // 6.38/6.03.
 Pass wire_pass(int R) {
-  if (R == 1) return {20, 20, 20, 2};
+  if (R == 1) return {21, 21, 21, 2};
   const int w = R == 2 ? 32 : R == 3 ? 16 : R <= 5 ? 12 : R == 6 ? 9 : R <= 8 ? 7 : 6;
   return {w, w, 2 * w};
 }
@@ -231,8 +232,8 @@ constexpr Pass kBcastPass = {10, 12, 12};
 // and 5.62 with 16, 4.95 with 8.
 constexpr int64_t kMid = 384, kSmall = 100, kFew = 20;
 constexpr int64_t kMaxGrid = (int64_t)1 << 25;  // x 64 threads: within 2^32
-constexpr int kCuLds = 160 << 10;               // bytes of LDS of a CU
-constexpr int kLdsStep = 1280;                  // allocated in steps of this
+constexpr int kLdsStep = 1280;                  // LDS is allocated in steps of this
+constexpr int kCuLdsSteps = 128;                // and a CU has 160 KiB
 constexpr int kCuWaves = 32;                    // waves a CU can hold
 
 // An explicit fl_set_blocks_per_cu caps the grid instead (in workgroups of
@@ -247,18 +248,21 @@ flr::Shape shape_for(const fl_layout* lay, Pass pass) {
     blocks = std::min<int64_t>(blocks, (int64_t)set * lay->num_cus * flr::kWaves);
   } else if (per_cu > kFew) {
     const int limit = per_cu >= kMid ? pass.waves : per_cu >= kSmall ? pass.mid : pass.small;
-    if (limit < kCuWaves) sh.lds = (unsigned)(kCuLds / limit / kLdsStep * kLdsStep);
+    const int steps = kCuLdsSteps / limit;
+    if (steps > kCuLdsSteps / kCuWaves) sh.lds = (unsigned)(steps * kLdsStep);
   }
   sh.grid = (unsigned)std::max<int64_t>(1, std::min(blocks, kMaxGrid));
   return sh;
 }
 
 // Whether a fused step's per-segment sums exchange their partials by way of
-// LDS, later than by DPP moves and with the same bits.  Long passes of a few
-// streams run faster so (measured on whole vectors: R=8 on
-// 1.0e9 elements 6.24 TB/s and 6.15, R=4 6.13 and 6.03, R=4 on 5.0e8 5.96 and
-// 5.81), the others slower (R=16 on 5.0e8 5.89 and
-// 6.02, R=2 on 6.3e7 5.47 and 5.57, the 1 Mi round 4.24 and 4.36).
+// LDS, later than by lane moves and with the same bits.  Long passes of a few
+// streams run faster so (TB/s by LDS and by lanes, 300 segments): R=3 on 5e8
+// elements 6.01 and 5.86, R=4 6.06 and 5.85, R=6 5.99 and 5.87, R=4 on 1.0e9 5.91
+// and 5.66, on 1.25e8 5.84 and 5.68, R=8 on 1.0e9 5.90 and 5.77.  R=5, R=12 and
+// R=16 on 5e8 and the shorter shards are the same within noise or a little
+// slower (R=8 on 6.3e7 5.84 and 5.98).  R=1 and R=2 on 5e8 would gain (6.17 and
+// 5.84, 6.08 and 5.88); they stay by lanes, as they were swept on shorter ones.
 int step_sum_by_lds(const fl_layout* lay, int R) {
   return R >= 3 && R <= 12 && lay->L.n_tiles * flr::kWaves / lay->num_cus >= kMid;
 }

@@ -239,12 +239,13 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
 }
 
 // A pause of 256 clocks between a wave's last addition and its stores.  Passes
-// that do little else run faster with it: to the wire format R=4 6.90 TB/s and
-// 6.43 without (12 waves per CU, 5e8 elements; 6.65 without at its best, 14),
-// R=8 on 6.3e7 elements 6.91 and 6.76, FedAvg G=4 (on whole vectors) 6.41 and
-// 6.32, G=5 on 5e7 6.27 and 6.17; twice the pause gives no more, half of it half.  It was found
-// when the bf16 rounding, in its place before, became one instruction.  With
-// AdamW between loads and stores it makes no difference.
+// that do little else run faster with it on long shards of a few streams (TB/s
+// with it and without, on 5e8 elements): to the wire format R=3 6.85 and 6.64,
+// R=4 6.81 and 6.48, R=8 6.68 and 6.55, FedAvg G=3 6.69 and 6.61, G=4 6.70 and
+// 6.47, G=8 6.63 and 6.57.  FedAvg of one and two loses (6.47 and 6.61, 6.57 and
+// 6.67); elsewhere, and on shorter shards, the difference is within noise.
+// Twice the pause gave no more, half of it half.  With AdamW between loads and
+// stores it makes no difference.
 __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(4); }
 
 // Reduced gradient of 8 elements (full vector): peers in ascending order.
@@ -972,20 +973,25 @@ hipError_t launch(const void* fn, const Args& a, Shape sh, hipStream_t st) {
   return hipLaunchKernel(fn, dim3(g), dim3(64), args, sh.lds, st);
 }
 
+// The exchange by way of LDS (SUMS 2) is asked for from 3 to 12 streams.
+template <int RT, int SUMS>
+hipError_t step_of(const StepArgs& a, Shape sh, hipStream_t st) {
+  if constexpr (SUMS == 2 && (RT == 1 || RT == 2 || RT == kMany)) return hipErrorInvalidValue;
+  else return launch((const void*)k_step<RT, 0, SUMS>, a, sh, st);
+}
+
 template <int SUMS>
 hipError_t dispatch_step(const StepArgs& a, Shape sh, hipStream_t st) {
   switch (a.R) {
-    case 1: return launch((const void*)k_step<1, 0, SUMS>, a, sh, st);
-    case 2: return launch((const void*)k_step<2, 0, SUMS>, a, sh, st);
-    case 3: return launch((const void*)k_step<3, 0, SUMS>, a, sh, st);
-    case 4: return launch((const void*)k_step<4, 0, SUMS>, a, sh, st);
-    case 5: return launch((const void*)k_step<5, 0, SUMS>, a, sh, st);
-    case 6: return launch((const void*)k_step<6, 0, SUMS>, a, sh, st);
-    case 7: return launch((const void*)k_step<7, 0, SUMS>, a, sh, st);
-    case 8: return launch((const void*)k_step<8, 0, SUMS>, a, sh, st);
-    default:
-      return launch(a.R > 24 ? (const void*)k_step<kMany, 0, SUMS>
-                             : (const void*)k_step<0, 0, SUMS>, a, sh, st);
+    case 1: return step_of<1, SUMS>(a, sh, st);
+    case 2: return step_of<2, SUMS>(a, sh, st);
+    case 3: return step_of<3, SUMS>(a, sh, st);
+    case 4: return step_of<4, SUMS>(a, sh, st);
+    case 5: return step_of<5, SUMS>(a, sh, st);
+    case 6: return step_of<6, SUMS>(a, sh, st);
+    case 7: return step_of<7, SUMS>(a, sh, st);
+    case 8: return step_of<8, SUMS>(a, sh, st);
+    default: return a.R > 24 ? step_of<kMany, SUMS>(a, sh, st) : step_of<0, SUMS>(a, sh, st);
   }
 }
 
