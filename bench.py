@@ -71,36 +71,36 @@ def read_traffic(workload, current_hash):
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
-def _rt(k):
-    """Template count of a dispatched kernel (the generic instance is 0)."""
-    return k if k <= 8 else 0
+# The kernel of each streaming pass, whatever instance of it the library
+# dispatched (a traced round launches one of each pass).
+STEP, ADAMW = r"k_step<\d+, 0, \d+>", r"k_step<\d+, 2, \d+>"
+TO_F32, TO_WIRE, SUMS = (r"k_reduce<\d+, %d, \w+, \d+>" % out for out in (1, 3, 4))
+FEDAVG, OUTER, RECV = r"k_fedavg<\d+, false>", r"k_fedavg<\d+, true>", r"k_bcast_recv\b"
 
 
 def round_kernels(w):
-    """(kernel name, algorithmic bytes read, bytes written) per launch for each
-    streaming kernel a round of workload w launches (bench.py asks for the
+    """(kernel pattern, algorithmic bytes read, bytes written) per launch for
+    each streaming pass of a round of workload w (bench.py asks for the
     per-segment sums in every round)."""
     n = w.n
     ks = []
     r = w.H if w.H > 1 else w.R
-    rt = 99 if r > 24 else _rt(r)   # the step's generic count on whole vectors
     if w.H > 1:
-        wire = "k_reduce<%d, 3, false, %d>" % (_rt(w.R), 2 if w.R == 1 else 1)
-        ks.append((wire, 2 * w.R * n, 2 * n))
+        ks.append((TO_WIRE, 2 * w.R * n, 2 * n))
     if w.max_grad_norm > 0 and w.H == 1 and w.clip_scratch:
-        ks.append(("k_reduce<%d, 1, true, 1>" % _rt(w.R), 2 * w.R * n, 4 * n))
-        ks.append(("k_step<1, 2, 0>", 16 * n, 14 * n))
+        ks.append((TO_F32, 2 * w.R * n, 4 * n))
+        ks.append((ADAMW, 16 * n, 14 * n))
     elif w.max_grad_norm > 0:
-        ks.append(("k_reduce<%d, 4, true, %d>" % (_rt(r), 4 if r <= 2 else 1), 2 * r * n, 0))
-        ks.append(("k_step<%d, 0, 0>" % rt, (2 * r + 12) * n, 14 * n))
+        ks.append((SUMS, 2 * r * n, 0))
+        ks.append((STEP, (2 * r + 12) * n, 14 * n))
     else:
-        ks.append(("k_step<%d, 0, %d>" % (rt, 2 if 3 <= r <= 12 and n >= 384 << 17 else 1), (2 * r + 12) * n, 14 * n))
+        ks.append((STEP, (2 * r + 12) * n, 14 * n))
     if w.H > 1 and not w.hsdp_member:
-        ks.append(("k_bcast_recv", 4 * n, 6 * n))
+        ks.append((RECV, 4 * n, 6 * n))
     elif w.outer is not None:
-        ks.append(("k_fedavg<%d, true>" % _rt(w.G), (2 * w.G + 8) * n, 14 * n))
+        ks.append((OUTER, (2 * w.G + 8) * n, 14 * n))
     else:
-        ks.append(("k_fedavg<%d, false>" % _rt(w.G), 2 * w.G * n, 6 * n))
+        ks.append((FEDAVG, 2 * w.G * n, 6 * n))
     return ks
 
 
@@ -127,14 +127,20 @@ def summarize_pmc(fetch_csv, write_csv, copy_mib, cmd_fetch, cmd_write, workload
     w = W_ALL()[workload]()
     fetch, write = _pmc_means(fetch_csv), _pmc_means(write_csv)
 
-    def pick(table, name):
-        """Mean and count over every dispatch of the kernel (all grid sizes:
-        a pass that carries the previous finalize has eight more workgroups)."""
-        hits = [v for (k, g), v in table.items() if name in k]
-        if not hits:
-            raise KeyError(name)
-        cnt = sum(c for _, c in hits)
-        return sum(m * c for m, c in hits) / cnt, cnt
+    def pick(table, pattern):
+        """The pass's kernel, its mean and its count over every dispatch (all
+        grid sizes: a pass that carries the previous finalize has eight more
+        workgroups)."""
+        hits = {}
+        for (k, g), v in table.items():
+            m = re.search(pattern, k)
+            if m:
+                hits.setdefault(m.group(0), []).append(v)
+        if len(hits) != 1:
+            raise KeyError("%s: %s" % (pattern, sorted(hits)))
+        (name, vs), = hits.items()
+        cnt = sum(c for _, c in vs)
+        return name, sum(m * c for m, c in vs) / cnt, cnt
 
     copy_kib = copy_mib * 1024.0
     cands = [(k, g) for (k, g) in fetch if COPY_KERNEL in k]
@@ -155,19 +161,19 @@ def summarize_pmc(fetch_csv, write_csv, copy_mib, cmd_fetch, cmd_write, workload
              "|---|---|---|---|---|---|---|---|---|"]
     out = {}
     kernels = round_kernels(w)
-    for name, alg_r, alg_w in kernels:
-        f, cnt = pick(fetch, name)
-        wr, _ = pick(write, name)
+    for pattern, alg_r, alg_w in kernels:
+        name, f, cnt = pick(fetch, pattern)
+        _, wr, _ = pick(write, pattern)
         rb, wb = f * f_scale * 1024, wr * w_scale * 1024
-        out[name] = rb + wb
+        out[name] = rb + wb   # (in the order of the passes)
         lines.append("| %s | %d | %.1f | %.1f | %.4f | %.4f | %.4f | %.4f | %.4f |" % (
             name, cnt, f, wr, rb / 1e9, wb / 1e9, alg_r / 1e9, alg_w / 1e9,
             (rb + wb) / (alg_r + alg_w)))
-    step = kernels[:-1]
+    step = list(out)[:-1]
     lines += ["", "Values read by bench.py (roofline.traffic: the HBM bytes of one local step, "
-              "the kernels %s):" % ", ".join(k for k, _, _ in step), "",
+              "the kernels %s):" % ", ".join(step), "",
               "- kernel_source_hash: %s" % kernel_source_hash(),
-              "- hbm_bytes_per_local_step: %.0f" % sum(out[k] for k, _, _ in step), ""]
+              "- hbm_bytes_per_local_step: %.0f" % sum(out[k] for k in step), ""]
     return "\n".join(lines)
 
 

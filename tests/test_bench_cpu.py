@@ -102,6 +102,25 @@ def test_trace_summary_format(tmp_path):
     assert "| k_step<8, 0, true>(flr::StepArgs) | 8 | 8000.0 | 7900.0 | 8100.0 | 90.00 % |" in out
 
 
+@pytest.mark.parametrize("instance", ["k_step<8, 0, 1>", "k_step<0, 0, 2>"])
+def test_traffic_summary_takes_the_instance_that_ran(tmp_path, instance):
+    """Which instance of a pass's kernel runs is the library's choice; the
+    summary names the one in the counter file."""
+    w = W.llama8b_s8()
+    rows = {"FETCH_SIZE": (28 * w.n, 8 * w.n), "WRITE_SIZE": (14 * w.n, 6 * w.n)}
+    paths = []
+    for counter, (step, fed) in rows.items():
+        p = tmp_path / (counter + ".csv")
+        p.write_text('"Kernel_Name","Grid_Size","Counter_Value"\n'
+                     + '"void flr::%s(flr::StepArgs)",64,%f\n' % (instance, step / 1024)
+                     + '"void flr::k_fedavg<4, false>(flr::FedArgs)",64,%f\n' % (fed / 1024)
+                     + '"__amd_rocclr_copyBuffer",64,%f\n' % (1024 * 1024))
+        paths.append(str(p))
+    out = bench.summarize_pmc(paths[0], paths[1], 1024, "a", "b", "llama8b_s8")
+    assert "| %s | 1 |" % instance in out
+    assert "- hbm_bytes_per_local_step: %d" % (42 * w.n) in out
+
+
 def test_cpu_baseline_runs_the_oracle_on_host_threads():
     cb = bench.cpu_baseline(W.llama8b_s8(), 1 << 16, min_seconds=0.5, n_one=1 << 15)
     assert cb["kind"] == "oracle" and cb["unit"] == "GB/s"
