@@ -86,11 +86,13 @@ def test_stream_counts(env, K, n):
     lay.close()
 
 
-# 256 CUs x 512 elements a unit: 20, 100 and 384 units per CU, each with a
-# length just inside and a ragged one just past it.
-@pytest.mark.parametrize("n", [u * 131072 + d for u in (20, 100, 384) for d in (0, 131072 + 3)])
-def test_launch_bands(env, n):
+# Units per CU on both sides of each threshold of the launch shape (no limit up
+# to 20; from 100 and from 384 on), at whole and at ragged lengths.
+@pytest.mark.parametrize("units,more", [(20, 0), (21, 3), (99, 3), (100, 0), (383, 3), (384, 0),
+                                        (384, 3)])
+def test_launch_bands(env, units, more):
     torch, P, orc = env
+    n = units * 512 * torch.cuda.get_device_properties(0).multi_processor_count + more
     off, dec, lay = _layout(P, n, 40, n)
     for K in (1, 2, 3):
         print("band n=%d K=%d" % (n, K), flush=True)
@@ -112,11 +114,30 @@ def test_launch_bands(env, n):
     work = torch.empty(n, dtype=torch.bfloat16, device="cuda")
     rm, r1, r2 = (t.cpu().numpy().copy() for t in (master, m, v))
     rw = np.zeros(n, np.uint16)
-    P.fl_local_step(lay, ADAMW, 3, peers, 1.0 / 3, master, m, v, work)
+    ss.fill_(-1.0)   # (units cut by segment boundaries, at three peers)
+    P.fl_local_step(lay, ADAMW, 3, peers, 1.0 / 3, master, m, v, work, seg_sumsq=ss)
     orc.adamw_step(off, dec, ADAMW, 3, want, rm, r1, r2, rw)
     H.assert_state_parity("step", dict(master=master.cpu().numpy(), m=m.cpu().numpy(),
                                        v=v.cpu().numpy(), working=H.to_u16(work)),
                           dict(master=rm, m=r1, v=r2, working=rw), bitwise=True)
+    H.assert_sumsq("step", ss.cpu().numpy(), orc.seg_sumsq(off, want))
+
+    print("band n=%d FedAvg, outer step, receive" % n, flush=True)
+    weights = [1.0, 2.0, 3.0]
+    P.fl_fedavg(lay, peers, weights, master, work)
+    fm, fw = orc.fedavg(host, weights)
+    assert np.array_equal(master.cpu().numpy().view(np.uint32), fm.view(np.uint32))
+    assert np.array_equal(H.to_u16(work), fw)
+    outer = dict(lr=0.7, momentum=0.9, nesterov=True)
+    prev, buf = (torch.empty(n, device="cuda").normal_(0.0, s) for s in (0.02, 1e-4))
+    rp, rb = prev.cpu().numpy().copy(), buf.cpu().numpy().copy()
+    P.fl_fedopt(lay, peers, weights, outer, prev, buf, master, work)
+    orc.fedopt(host, weights, outer, rp, rb, rm, rw)
+    for t, r in ((prev, rp), (buf, rb), (master, rm)):
+        assert np.array_equal(t.cpu().numpy().view(np.uint32), r.view(np.uint32))
+    assert np.array_equal(H.to_u16(work), rw)
+    P.fl_broadcast_recv(lay, m, prev, work)
+    assert torch.equal(prev, m) and torch.equal(work, m.bfloat16())
     lay.close()
 
 
