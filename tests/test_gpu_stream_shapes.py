@@ -182,3 +182,61 @@ def test_adamw_operand_ranges(env, eps, beta2, t):
                                          v=dev[3].cpu().numpy(), working=H.to_u16(work)),
                           dict(master=p, m=m, v=v, working=rw), bitwise=True)
     lay.close()
+
+
+def test_every_float_to_bf16(env):
+    """The conversion of all 2^32 floats, by the broadcast receive, against
+    rounding to nearest even on the bits (a NaN keeps its sign and upper bits
+    and becomes quiet)."""
+    torch, P, _ = env
+    n = 1 << 28
+    lay = P.Layout(np.array([0, n], np.int64), np.ones(1, np.uint8))
+    master = torch.empty(n, device="cuda")
+    work = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    for k in range(16):
+        print("floats %d of 16" % k, flush=True)
+        lo = (k << 28) - (1 << 31)
+        bits = torch.arange(lo, lo + n, dtype=torch.int64, device="cuda")
+        recv = bits.to(torch.int32).view(torch.float32)
+        P.fl_broadcast_recv(lay, recv, master, work)
+        assert torch.equal(master.view(torch.int32), recv.view(torch.int32))
+        bits &= 0xFFFFFFFF
+        want = (bits + 0x7FFF + ((bits >> 16) & 1)) >> 16
+        want = torch.where((bits & 0x7FFFFFFF) > 0x7F800000, (bits >> 16) | 0x40, want)
+        got = work.view(torch.int16).to(torch.int64) & 0xFFFF
+        assert torch.equal(got, want)
+    lay.close()
+
+
+@pytest.mark.parametrize("exponent,t", [(-100, 1000), (0, 1000), (58, 1000), (0, 1)])
+def test_every_mantissa_of_the_root(env, exponent, t):
+    """The short form of the root for all floats of two binades: at both ends
+    of its range and in the middle, the bias correction 1 (t = 1000) or the
+    root of a half.  With these hyperparameters a step halves m and v and moves
+    p from 0 to -lr_t m / (sqrt(v) / bc2 + eps), and with m just under the
+    denominator the quotient shows each unit in the last place of the root."""
+    torch, P, _ = env
+    hp = dict(lr=1.0, beta1=0.5, beta2=0.5, eps=2.0 ** -60, weight_decay=0.0)
+    f = np.float32
+    one = (np.arange(1 << 23, dtype=np.uint32) | np.uint32(127 << 23)).view(f)
+    v = np.concatenate([np.ldexp(one, exponent), np.ldexp(one, exponent + 1)])
+    bc2, lr = f(np.sqrt(1.0 - 0.5 ** t)), f(1.0 / (1.0 - 0.5 ** t))
+
+    def quotient(root, m):
+        return m / (root / bc2 + f(2.0 ** -60))
+
+    root = np.sqrt(v)
+    m = (root / bc2 + f(2.0 ** -60)) * f(1.0 - 2.0 ** -21)
+    want = quotient(root, m)
+    assert m.dtype == want.dtype == f
+    if t == 1000:   # (an error in the root shows)
+        for to in (np.inf, 0.0):
+            assert np.mean(quotient(np.nextafter(root, f(to)), m) == want) < 1e-3
+    lay = P.Layout(np.array([0, v.size], np.int64), np.ones(1, np.uint8))
+    g, p = torch.zeros(v.size, device="cuda"), torch.zeros(v.size, device="cuda")
+    dm, dv = torch.from_numpy(2 * m).cuda(), torch.from_numpy(2 * v).cuda()
+    print("roots from 2^%d, t=%d" % (exponent, t), flush=True)
+    P.fl_adamw_step(lay, hp, t, g, p, dm, dv, None)
+    assert np.array_equal(dv.cpu().numpy(), v) and np.array_equal(dm.cpu().numpy(), m)
+    assert np.array_equal(p.cpu().numpy(), -(lr * want))
+    lay.close()
