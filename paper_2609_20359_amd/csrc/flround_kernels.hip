@@ -590,8 +590,9 @@ __device__ __forceinline__ Place place(const Carry& c) {
 // operands at the ends of the range.  When no lane of the wave has one (kLo,
 // kHi below, and s.rbc2, which the host sets when eps and bc2_sqrt allow), the
 // same results come cheaper:
-//  - sqrt: x * rsq(x) with one correction by its exact residual; equal to the
-//    correctly rounded root for every float from 2^-100 to 2^120;
+//  - sqrt: x * rsq(x) with one correction by its exact residual.  That it is the
+//    correctly rounded root rests on the values the instruction returns, so the
+//    tests compare every float of the range;
 //  - / bc2_sqrt: by its correctly rounded reciprocal and two corrections (the
 //    first makes the quotient faithful, the second by Markstein's theorem
 //    correctly rounded);

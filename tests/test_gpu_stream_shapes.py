@@ -240,3 +240,23 @@ def test_every_mantissa_of_the_root(env, exponent, t):
     assert np.array_equal(dv.cpu().numpy(), v) and np.array_equal(dm.cpu().numpy(), m)
     assert np.array_equal(p.cpu().numpy(), -(lr * want))
     lay.close()
+
+
+def test_root_over_its_whole_range(env):
+    """The same quotients for every float from 2^-100 to 2^60, the roots and
+    quotients of the reference rounded from double (which is exact for both)."""
+    torch, P, _ = env
+    hp = dict(lr=1.0, beta1=0.5, beta2=0.5, eps=2.0 ** -60, weight_decay=0.0)
+    n = 1 << 24
+    lay = P.Layout(np.array([0, n], np.int64), np.ones(1, np.uint8))
+    g, mantissas = torch.zeros(n, device="cuda"), torch.arange(n, dtype=torch.int32, device="cuda")
+    print("roots from 2^-100 to 2^60", flush=True)
+    for exponent in range(-100, 60, 2):
+        v = (mantissas + ((exponent + 127) << 23)).view(torch.float32)
+        den = v.double().sqrt().float() + 2.0 ** -60
+        m = den * (1.0 - 2.0 ** -21)
+        p, dm, dv = torch.zeros(n, device="cuda"), 2 * m, 2 * v
+        P.fl_adamw_step(lay, hp, 1000, g, p, dm, dv, None)
+        assert torch.equal(dv, v) and torch.equal(dm, m)
+        assert torch.equal(p, -(m.double() / den.double()).float()), exponent
+    lay.close()
