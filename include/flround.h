@@ -439,6 +439,11 @@ int fl_round_hsdp(const fl_layout* layout, const fl_round_cfg* cfg, const fl_hsd
  * defaults (a wave for every 512 elements, started in order, with a limit per
  * pass on how many a CU holds at once).  Process-wide; returns the previous
  * value.
+ * With the defaults a pass refills the GPU until its last wave has started.
+ * A kernel on another stream that needs most of a CU's LDS or registers (a
+ * large matrix product) then starts when the pass ends, while smaller ones run
+ * in between.  With 1 such kernels run beside the pass, which takes about an
+ * eighth longer.
  * ---------------------------------------------------------------------- */
 int fl_set_blocks_per_cu(int blocks_per_cu);
 
