@@ -238,6 +238,121 @@ __device__ __forceinline__ void sum_streams(Ptr ptr, int n, Add add) {
   }
 }
 
+// The unit that the shard's end cuts: a lane holds the elements below `left`
+// (its own first one is 0), the others are 0 and stay unwritten.  A group of four
+// is read or written at once where it is whole, as in the other units; of the one
+// group cut inside (n not a multiple of four) the elements are.  And all loads of
+// a chunk of streams are out before its first addition.  One element and stream
+// after another instead, this unit took 3 us at 8 streams and 66 at 64, longer
+// than a short pass: with 64 streams the reduction of 65,000 elements took 64 us
+// and takes 23 (the call from Python), the sums of 1.4e7 346 and 272, the wire
+// format of 3e6 with 8 streams 14.1 and 11.1.
+template <int kGap>
+__device__ __forceinline__ bool whole(int h, int left) { return left >= h * kGap + 4; }
+
+template <int kGap>
+__device__ __forceinline__ void load_f32x8_cut(const float* p, int left, float x[8]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    f32x4 a{};
+    if (whole<kGap>(h, left)) {
+      a = ld(reinterpret_cast<const f32x4*>(p + h * kGap));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (h * kGap + e < left) a[e] = p[h * kGap + e];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[4 * h + e] = a[e];
+  }
+}
+
+template <int kGap>
+__device__ __forceinline__ void store_f32x8_cut(float* p, int left, const float x[8]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float* y = x + 4 * h;
+    if (whole<kGap>(h, left)) {
+      st(reinterpret_cast<f32x4*>(p + h * kGap), f32x4{y[0], y[1], y[2], y[3]});
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (h * kGap + e < left) p[h * kGap + e] = y[e];
+    }
+  }
+}
+
+template <int kGap>
+__device__ __forceinline__ void store_bf16x8_cut(uint16_t* p, int left, const float x[8]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float* y = x + 4 * h;
+    if (whole<kGap>(h, left)) {
+      st(reinterpret_cast<u32x2*>(p + h * kGap),
+         u32x2{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])});
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (h * kGap + e < left) p[h * kGap + e] = (uint16_t)to_bf16(y[e]);
+    }
+  }
+}
+
+// sum_streams for that unit, of the arrays' elements base (the lane's first) to
+// end.  The elements of the group cut inside come stream by lane: lane k loads
+// stream k's, and each stream's go to the lane that holds the group.  At most four
+// compiled streams at a time: this path shall not cost the others registers.
+static_assert(kMaxPeers <= 64, "a lane for each stream");
+
+template <int N, int kGap, typename Array, typename Add>
+__device__ __forceinline__ void sum_streams_cut(Array array, int n, int64_t base, int64_t end,
+                                                Add add) {
+  constexpr int kMost = N == 0 ? kChunk : N <= 4 ? N : 4;
+  const int left = (int)(end - base);
+  int some = (int)(end & 3);
+  asm volatile("" : "+s"(some));  // (not kept in registers by the whole units)
+  const bool in0 = some && left == some, in1 = some && left == kGap + some;
+  uint32_t c0 = 0, c1 = 0;
+  if (some && (int)threadIdx.x < n) {
+    const uint16_t* p = array((int)threadIdx.x) + (end - some);
+    const uint32_t x = p[0], y = p[some > 1 ? 1 : 0], z = p[some > 2 ? 2 : 0];
+    c0 = some > 1 ? x | y << 16 : x;
+    c1 = some > 2 ? z : 0;
+  }
+  for (int k0 = 0; k0 < n; k0 += kMost) {
+    const uint16_t* p[kMost];
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) p[k] = array(kMost == N || k0 + k < n ? k0 + k : n - 1);
+    u32x4 w[kMost] = {};
+    if (whole<kGap>(0, left)) {
+#pragma unroll
+      for (int k = 0; k < kMost; ++k) {
+        const u32x2 x = ld_once(reinterpret_cast<const u32x2*>(p[k] + base));
+        w[k].x = x.x;
+        w[k].y = x.y;
+      }
+    }
+    if (whole<kGap>(1, left)) {
+#pragma unroll
+      for (int k = 0; k < kMost; ++k) {
+        const u32x2 x = ld_once(reinterpret_cast<const u32x2*>(p[k] + base + kGap));
+        w[k].z = x.x;
+        w[k].w = x.y;
+      }
+    }
+    loads_out();
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+      if (kMost == N || k0 + k < n) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)c0, k0 + k);
+        const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)c1, k0 + k);
+        add(k0 + k, u32x4{in0 ? x : w[k].x, in0 ? y : w[k].y, in1 ? x : w[k].z,
+                          in1 ? y : w[k].w});
+      }
+    }
+  }
+}
+
 // A pause of 256 clocks between a wave's last addition and its stores.  Passes
 // that do little else run faster with it on long shards of a few streams (TB/s
 // with it and without, on 5e8 elements): to the wire format R=3 6.85 and 6.64,
@@ -258,19 +373,14 @@ __device__ __forceinline__ void reduce_vec(const StepArgs& a, int64_t base, floa
   for (int e = 0; e < 8; ++e) g[e] = acc[e] * a.grad_scale;
 }
 
-// Same for a unit that the shard's end cuts: one element at a time, 0 past it.
-template <int kGap>
-__device__ __forceinline__ void reduce_some(const StepArgs& a, int64_t base, float g[8]) {
+// Same for a unit that the shard's end cuts: 0 past it.
+template <int RT, int kGap>
+__device__ __forceinline__ void reduce_cut(const StepArgs& a, int64_t base, float g[8]) {
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  sum_streams_cut<RT, kGap>([&](int r) { return a.grads[r]; }, a.R, base, a.L.n,
+                            [&](int, u32x4 w) { add_bf16x8(acc, w); });
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int64_t i = base + (e / 4) * kGap + e % 4;
-    float acc = 0.f;
-    if (i < a.L.n) {
-      for (int r = 0; r < a.R; ++r)
-        acc = acc + __uint_as_float((uint32_t)a.grads[r][i] << 16);
-    }
-    g[e] = i < a.L.n ? acc * a.grad_scale : 0.f;
-  }
+  for (int e = 0; e < 8; ++e) g[e] = acc[e] * a.grad_scale;
 }
 
 // Fixed-tree sum over one wave64, all lanes active: the butterfly of
@@ -686,18 +796,12 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
         reduce_vec<kStreams, kGap>(a, base, g);
       }
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = base + (e / 4) * kGap + e % 4;
-        p[e] = 0.f; m[e] = 0.f; v[e] = 0.f; g[e] = 0.f;
-        if (i < a.L.n) {
-          p[e] = a.master[i];
-          m[e] = a.m[i];
-          v[e] = a.v[i];
-          if constexpr (MODE == 2) g[e] = a.g_in[i];
-        }
-      }
-      if constexpr (MODE != 2) reduce_some<kGap>(a, base, g);
+      const int left = (int)(a.L.n - base);
+      load_f32x8_cut<kGap>(a.master + base, left, p);
+      load_f32x8_cut<kGap>(a.m + base, left, m);
+      load_f32x8_cut<kGap>(a.v + base, left, v);
+      if constexpr (MODE == 2) load_f32x8_cut<kGap>(a.g_in + base, left, g);
+      else reduce_cut<kStreams, kGap>(a, base, g);
     }
 
     // (not looked at before the streams' loads are out)
@@ -731,16 +835,11 @@ __global__ void __launch_bounds__(64) k_step(const StepArgs a) {
       store_f32x8<kGap>(a.v + base, v);
       if (MODE == 0 || a.working) store_bf16x8<kGap>(a.working + base, p);
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = base + (e / 4) * kGap + e % 4;
-        if (i < a.L.n) {
-          a.master[i] = p[e];
-          a.m[i] = m[e];
-          a.v[i] = v[e];
-          if (MODE == 0 || a.working) a.working[i] = (uint16_t)to_bf16(p[e]);
-        }
-      }
+      const int left = (int)(a.L.n - base);
+      store_f32x8_cut<kGap>(a.master + base, left, p);
+      store_f32x8_cut<kGap>(a.m + base, left, m);
+      store_f32x8_cut<kGap>(a.v + base, left, v);
+      if (MODE == 0 || a.working) store_bf16x8_cut<kGap>(a.working + base, left, p);
     }
     if constexpr (SUMS != 0) unit_sumsq<kGap, SUMS == 2>(a.partials, us, u, lane, seg, g);
   }
@@ -789,7 +888,7 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
     } else {
 #pragma unroll
       for (int i = 0; i < NV; ++i)
-        reduce_some<kGap>(a, (u0 + i) * kUnit + at, g[i]);
+        reduce_cut<RT, kGap>(a, (u0 + i) * kUnit + at, g[i]);
     }
     if constexpr (OUT == 3) pause();
 #pragma unroll
@@ -803,14 +902,8 @@ __global__ void __launch_bounds__(64) k_reduce(const StepArgs a) {
       }
       if constexpr (OUT != 4) {
         if (!full) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int64_t k = base + (e / 4) * kGap + e % 4;
-            if (k < a.L.n) {
-              if constexpr (OUT == 1) a.g_out[k] = g[i][e];
-              else a.wire_out[k] = (uint16_t)to_bf16(g[i][e]);
-            }
-          }
+          if constexpr (OUT == 1) store_f32x8_cut<kGap>(a.g_out + base, (int)(a.L.n - base), g[i]);
+          else store_bf16x8_cut<kGap>(a.wire_out + base, (int)(a.L.n - base), g[i]);
         }
       }
       if constexpr (SUMSQ) {
@@ -838,6 +931,7 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
   for (int64_t u = w.at; u < n_units; u += w.stride) {
     const int64_t base = u * kUnit + w.lane * 4;
     const bool full = (u + 1) * kUnit <= a.n;
+    const int left = (int)(a.n - base);   // (of the unit that is cut)
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float prev[8] = {}, buf[8] = {};
     if (full) {
@@ -848,18 +942,12 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
       sum_streams<GT, kHalves>([&](int k) { return a.reps[k] + base; }, a.G,
                                [&](int k, u32x4 x) { fma_free_bf16x8(acc, a.w[k], x); });
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = base + (e / 4) * kHalves + e % 4;
-        if (i < a.n) {
-          for (int k = 0; k < a.G; ++k)
-            acc[e] = acc[e] + (a.w[k] * __uint_as_float((uint32_t)a.reps[k][i] << 16));
-          if constexpr (OUTER) {
-            prev[e] = a.prev[i];
-            buf[e] = a.buf[i];
-          }
-        }
+      if constexpr (OUTER) {
+        load_f32x8_cut<kHalves>(a.prev + base, left, prev);
+        load_f32x8_cut<kHalves>(a.buf + base, left, buf);
       }
+      sum_streams_cut<GT, kHalves>([&](int k) { return a.reps[k]; }, a.G, base, a.n,
+                                   [&](int k, u32x4 x) { fma_free_bf16x8(acc, a.w[k], x); });
     }
     if constexpr (OUTER) {
 #pragma unroll
@@ -880,17 +968,11 @@ __global__ void __launch_bounds__(64) k_fedavg(const FedArgs a) {
         store_f32x8<kHalves>(a.buf + base, buf);
       }
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = base + (e / 4) * kHalves + e % 4;
-        if (i < a.n) {
-          a.master[i] = acc[e];
-          a.working[i] = (uint16_t)to_bf16(acc[e]);
-          if constexpr (OUTER) {
-            a.prev[i] = acc[e];
-            a.buf[i] = buf[e];
-          }
-        }
+      store_f32x8_cut<kHalves>(a.master + base, left, acc);
+      store_bf16x8_cut<kHalves>(a.working + base, left, acc);
+      if constexpr (OUTER) {
+        store_f32x8_cut<kHalves>(a.prev + base, left, acc);
+        store_f32x8_cut<kHalves>(a.buf + base, left, buf);
       }
     }
   }
@@ -954,14 +1036,11 @@ __global__ void __launch_bounds__(64) k_bcast_recv(const BcastArgs a) {
       store_f32x8<kHalves>(a.master + base, x);
       store_bf16x8<kHalves>(a.working + base, x);
     } else {
-      for (int e = 0; e < 8; ++e) {
-        const int64_t i = base + (e / 4) * kHalves + e % 4;
-        if (i < n) {
-          const float x = a.recv[i];
-          a.master[i] = x;
-          a.working[i] = (uint16_t)to_bf16(x);
-        }
-      }
+      const int left = (int)(n - base);
+      float x[8];
+      load_f32x8_cut<kHalves>(a.recv + base, left, x);
+      store_f32x8_cut<kHalves>(a.master + base, left, x);
+      store_bf16x8_cut<kHalves>(a.working + base, left, x);
     }
   }
 }

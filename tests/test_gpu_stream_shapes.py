@@ -86,6 +86,89 @@ def test_stream_counts(env, K, n):
     lay.close()
 
 
+# The last unit when the shard's end cuts it: in either half, at and inside a
+# group of four, and shards of less than a group.
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 64])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 8, 254, 256, 257, 259, 510, 512 + 4, 4 * 512 - 1])
+def test_cut_units(env, K, n):
+    torch, P, orc = env
+    test_stream_counts(env, K, n)
+    off, dec, lay = _layout(P, n, 3, n + K)
+    reps = [_bf16(torch, n, 2e-2, k) for k in range(K)]
+    weights = 1.0 + np.arange(K) % 3
+    outer = dict(lr=0.7, momentum=0.9, nesterov=False)
+    prev, buf = (torch.empty(n, device="cuda").normal_(0.0, s) for s in (0.02, 1e-4))
+    master, recv = torch.empty(n, device="cuda"), torch.empty(n, device="cuda").normal_()
+    work = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    rp, rb, rm = (t.cpu().numpy().copy() for t in (prev, buf, master))
+    rw = np.zeros(n, np.uint16)
+    print("cut outer K=%d n=%d" % (K, n), flush=True)
+    P.fl_fedopt(lay, reps, weights, outer, prev, buf, master, work)
+    orc.fedopt([H.to_u16(t) for t in reps], weights, outer, rp, rb, rm, rw)
+    for t, r in ((prev, rp), (buf, rb), (master, rm)):
+        assert np.array_equal(t.cpu().numpy().view(np.uint32), r.view(np.uint32))
+    assert np.array_equal(H.to_u16(work), rw)
+    P.fl_broadcast_recv(lay, recv, master, work)
+    assert torch.equal(master, recv) and torch.equal(work, recv.bfloat16())
+    lay.close()
+
+
+def test_cut_units_write_nothing_past_the_end(env):
+    """What lies behind a shard's arrays stays as it is."""
+    torch, P, _ = env
+    room = 512
+    for n in (1, 3, 255, 257, 513, 1022):
+        off, dec, lay = _layout(P, n, 1, n)
+
+        def arr(dt, fill):
+            return torch.full((n + room,), fill, dtype=dt, device="cuda")
+
+        g = [arr(torch.bfloat16, 1e-3) for _ in range(3)]
+        f = {k: arr(torch.float32, 0.25) for k in ("g", "master", "m", "v", "prev", "buf")}
+        w = arr(torch.bfloat16, 0.25)
+        s = {k: t[:n] for k, t in f.items()}
+        gs = [t[:n] for t in g]
+        print("past the end n=%d" % n, flush=True)
+        P.fl_shard_reduce(lay, gs, 1.0, s["g"])
+        P.fl_shard_reduce_wire(lay, gs, 1.0, w[:n])
+        P.fl_local_step(lay, ADAMW, 1, gs, 1.0, s["master"], s["m"], s["v"], w[:n])
+        P.fl_adamw_step(lay, ADAMW, 1, s["g"], s["master"], s["m"], s["v"], w[:n])
+        P.fl_fedavg(lay, gs, [1.0] * 3, s["master"], w[:n])
+        P.fl_fedopt(lay, gs, [1.0] * 3, dict(lr=0.7, momentum=0.9, nesterov=True), s["prev"],
+                    s["buf"], s["master"], w[:n])
+        P.fl_broadcast_recv(lay, s["v"], s["master"], w[:n])
+        for t in list(f.values()) + [w]:
+            assert torch.equal(t[n:], torch.full_like(t[n:], 0.25))
+        lay.close()
+
+
+def test_cut_unit_costs_no_more_than_a_whole_one(env):
+    """64 streams: a shard of one unit less an element, and the whole unit (one
+    element and stream after another, the first took 70 us, the second 33, which
+    is the call from Python)."""
+    torch, P, _ = env
+
+    def us(n, reps=40):
+        _, _, lay = _layout(P, n, 1, n)
+        peers = [_bf16(torch, n, 1e-3, k) for k in range(64)]
+        wire = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+        best = float("inf")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(reps):
+                P.fl_shard_reduce_wire(lay, peers, 1.0, wire)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / reps)
+        lay.close()
+        return best
+
+    whole, cut = us(512), us(511)
+    print("one unit %.1f us, less an element %.1f us" % (whole, cut), flush=True)
+    assert cut < 1.5 * whole
+
+
 # Units per CU on both sides of each threshold of the launch shape (no limit up
 # to 20; from 100 and from 384 on), at whole and at ragged lengths.
 @pytest.mark.parametrize("units,more", [(20, 0), (21, 3), (99, 3), (100, 0), (383, 3), (384, 0),
