@@ -113,6 +113,40 @@ def test_cut_units(env, K, n):
     lay.close()
 
 
+# Units of many segments: the search for the unit's and for each lane's.
+@pytest.mark.parametrize("R", [1, 4, 9, 26])
+@pytest.mark.parametrize("mean", [1, 3, 37, 700])
+def test_short_segments(env, R, mean):
+    torch, P, orc = env
+    n = 11 * 2048 + 515
+    r = np.random.default_rng(mean)
+    cuts = np.unique(r.integers(1, n, n // mean)) if mean > 1 else np.arange(1, n)
+    off = np.concatenate([[0], cuts, [n]]).astype(np.int64)
+    dec = r.integers(0, 2, off.size - 1).astype(np.uint8)
+    lay = P.Layout(off, dec)
+    peers = [_bf16(torch, n, 1e-3, k) for k in range(R)]
+    want = orc.shard_reduce([H.to_u16(t) for t in peers], 1.0 / R)
+    ref = orc.seg_sumsq(off, want)
+    p0, m0 = torch.empty(n, device="cuda").normal_(0.0, 0.02), torch.full((n,), 1e-5, device="cuda")
+    rm, r1, r2, rw = p0.cpu().numpy(), m0.cpu().numpy(), m0.cpu().numpy() ** 2, np.zeros(n, np.uint16)
+    orc.adamw_step(off, dec, ADAMW, 7, want, rm, r1, r2, rw)
+    for ss in (None, torch.full((off.size - 1,), -1.0, device="cuda")):
+        master, m = p0.clone(), m0.clone()
+        v, work = m0 ** 2, torch.empty(n, dtype=torch.bfloat16, device="cuda")
+        print("segments of %d R=%d sums=%s" % (mean, R, ss is not None), flush=True)
+        P.fl_local_step(lay, ADAMW, 7, peers, 1.0 / R, master, m, v, work, seg_sumsq=ss)
+        H.assert_state_parity("step", dict(master=master.cpu().numpy(), m=m.cpu().numpy(),
+                                           v=v.cpu().numpy(), working=H.to_u16(work)),
+                              dict(master=rm, m=r1, v=r2, working=rw.copy()), bitwise=True)
+    H.assert_sumsq("step", ss.cpu().numpy(), ref)
+    total = torch.zeros(1, dtype=torch.float64, device="cuda")
+    P.fl_grad_sumsq(lay, peers, 1.0 / R, total, seg_sumsq=ss.fill_(-1.0))
+    H.assert_sumsq("sums", ss.cpu().numpy(), ref)
+    P.fl_shard_reduce(lay, peers, 1.0 / R, m, seg_sumsq=ss.fill_(-1.0))
+    H.assert_sumsq("reduce", ss.cpu().numpy(), ref)
+    lay.close()
+
+
 def test_cut_units_write_nothing_past_the_end(env):
     """What lies behind a shard's arrays stays as it is."""
     torch, P, _ = env
