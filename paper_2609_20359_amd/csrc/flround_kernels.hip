@@ -310,7 +310,7 @@ __device__ __forceinline__ void sum_streams_cut(Array array, int n, int64_t base
   constexpr int kMost = N == 0 ? kChunk : N <= 4 ? N : 4;
   const int left = (int)(end - base);
   int some = (int)(end & 3);
-  asm volatile("" : "+s"(some));  // (not kept in registers by the whole units)
+  asm volatile("" : "+s"(some), "+s"(n));  // (not kept in registers by the whole units)
   const bool in0 = some && left == some, in1 = some && left == kGap + some;
   uint32_t c0 = 0, c1 = 0;
   if (some && (int)threadIdx.x < n) {
