@@ -26,10 +26,11 @@ on kind B the HIP runtime places them anew in each and the rate follows.
 The staggered pool gives the same rate on both, which is why it is the
 default; the same-design bandwidth probe, its streams placed either way,
 shows the same spread.  The library's kernels start their waves in address
-order, run that round in 54.9 ms in the staggered pool, and are as fast with
-any stagger from 0 to 68 KiB.  In the grid-stride loop, changing which workgroup walks which tiles (one
-contiguous range per workgroup, or chunks of 16 or 128 tiles dealt round
-robin) moved the probe's rate no more than a new placement does."""
+order, run that round in 54.2 ms in the staggered pool, and are as fast with
+any stagger from 0 to 68 KiB.  In the grid-stride loop, changing which
+workgroup walks which tiles (one contiguous range per workgroup, or chunks of
+16 or 128 tiles dealt round robin) moved the probe's rate no more than a new
+placement does."""
 import atexit
 import ctypes
 
