@@ -113,9 +113,10 @@ def test_cut_units(env, K, n):
     lay.close()
 
 
-# Units of many segments: the search for the unit's and for each lane's.
+# Units of several segments: tiles of up to 64 (a lane for each) and of more
+# (search); at a mean of 32 elements tiles have a few less and a few more than 64.
 @pytest.mark.parametrize("R", [1, 4, 9, 26])
-@pytest.mark.parametrize("mean", [1, 3, 37, 700])
+@pytest.mark.parametrize("mean", [1, 3, 32, 37, 700])
 def test_short_segments(env, R, mean):
     torch, P, orc = env
     n = 11 * 2048 + 515
@@ -123,6 +124,9 @@ def test_short_segments(env, R, mean):
     cuts = np.unique(r.integers(1, n, n // mean)) if mean > 1 else np.arange(1, n)
     off = np.concatenate([[0], cuts, [n]]).astype(np.int64)
     dec = r.integers(0, 2, off.size - 1).astype(np.uint8)
+    if mean == 32:
+        per = [np.sum((off[:-1] < t + 2048) & (off[1:] > t)) for t in range(0, n, 2048)]
+        assert min(per[:-1]) <= 64 < max(per)
     lay = P.Layout(off, dec)
     peers = [_bf16(torch, n, 1e-3, k) for k in range(R)]
     want = orc.shard_reduce([H.to_u16(t) for t in peers], 1.0 / R)
